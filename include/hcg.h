@@ -272,18 +272,12 @@ hcg_status hcg_grid(hcg_plan_t plan, const void* spectra, int64_t nchan, hcg_dty
  * memory during the call: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  Same arguments, kernels, results and
  * errors as hcg_grid; it calls no hipMalloc, hipFree or allocating library
- * routine.  Where hcg_grid takes stream-ordered memory for partial sums (the
- * FP32 form with nchan <= 8 on maps of fewer than 1024 8 x 8 tiles), this call
- * uses a static device array of HCG_NOALLOC_SCRATCH_BYTES per device, held by
- * each device the library runs on until the process ends (every such map
- * fits: it needs at most about 14 MB); a map that would need more is refused
- * with HCG_E_UNSUPPORTED.  The partial sums are written whole before they are
- * read, so nothing carries over from an earlier call.  All calls on one
- * device share that array: calls of hcg_grid_noalloc that overlap on one
- * device (on different streams, or from different host threads without
- * ordering) race and give wrong maps; calls on one stream are ordered and
- * safe.  The first call on a device looks up the array's device address
- * once (hipGetSymbolAddress, with that device current).
+ * routine.  Where hcg_grid puts the values of a few-channel map (FP32, nchan
+ * <= 8) into the plan's order in stream-ordered scratch first, this call reads
+ * them through the plan's permutation: the same sums in the same order.  It
+ * keeps no scratch, so calls may overlap.
+ * (HCG_NOALLOC_SCRATCH_BYTES: the static scratch of earlier versions, per
+ * device; no longer taken.)
  */
 #define HCG_NOALLOC_SCRATCH_BYTES (16u << 20)
 hcg_status hcg_grid_noalloc(hcg_plan_t plan, const void* spectra, int64_t nchan,

@@ -359,9 +359,7 @@ def hcg_grid(plan: Plan, spectra: torch.Tensor, cube: torch.Tensor, weights=None
 
 def hcg_grid_noalloc(plan: Plan, spectra: torch.Tensor, cube: torch.Tensor, weights=None,
                      dtype: int = HCG_F32, chan_scale=None, stream=None) -> None:
-    """``hcg_grid`` through the entry point that allocates no device memory
-    (its scratch is a static device array shared by every call on a device:
-    calls that overlap on one device race)."""
+    """``hcg_grid`` through the entry point that allocates no device memory."""
     _grid_call("hcg_grid_noalloc", plan, spectra, cube, weights, dtype, chan_scale, stream)
 
 

@@ -25,6 +25,7 @@
 #include <string>
 #include <vector>
 
+#include "cells_tile.h"
 #include "forms.h"
 #include "gather_tile.h"
 
@@ -88,29 +89,48 @@ __device__ inline BatchSeg batch_seg_of(const BatchSeg* __restrict__ segs, uint3
   return segs[lo];
 }
 
-// The few-channel class (FP32, C <= 8): one wave per tile, on dynamic LDS of
-// cells_batch_lds_bytes(maxr) with maxr the largest range count of the
-// batch's plans, in kernels of their own (bounded at 64 threads, not by the
-// matrix-core classes' 256-thread, two-per-CU bounds, so that they keep few
-// registers): many tiles in flight on a CU.  Items are tiles.
-//
-// One workgroup per item:
-__global__ void __launch_bounds__(64) k_cells_items(const GatherArgs* __restrict__ fields,
-                                                    const BatchSeg* __restrict__ segs,
-                                                    uint32_t nseg, int maxr) {
-  extern __shared__ __align__(16) unsigned char s_dyn[];
-  const uint32_t it = blockIdx.x;
-  const BatchSeg sg = batch_seg_of(segs, nseg, it);
-  gather_cells_tile(fields[sg.field], (int)(it - sg.base), cells_lds(s_dyn, maxr));
+// The few-channel class (FP32, C <= 8): four waves per tile, one sub-block
+// of cells each at a time (cells_tile.h), on dynamic LDS sized to the largest
+// range count of the batch's plans, in kernels of their own (not bound by the
+// matrix-core classes' registers): many tiles in flight on a CU.  Items are
+// tiles.
+constexpr int kCellsWaves = 4;
+
+// Sub-blocks 4 part .. 4 part + 3 of a tile (C = 1 has part 0 only, C <= 8
+// parts 0 .. 3).
+constexpr int kCellsParts = CellsShape<8, false>::kSubs / kCellsWaves;
+template <bool kWide>
+__device__ inline void cells_item(const GatherArgs& a, int tile, int part, unsigned char* lds) {
+  if (a.C == 1) cells_tile<1, false, kWide, false>(a, tile, 0, kCellsWaves, 1, lds);
+  else cells_tile<8, false, kWide, false>(a, tile, part * kCellsWaves, kCellsWaves, 1, lds);
+}
+static_assert(CellsShape<1, false>::kSubs == kCellsWaves, "one sub-block per wave at C = 1");
+constexpr size_t cells_batch_lds_bytes(int maxr) {
+  const size_t one = cells_lds_size<16, 2, false>(kCellsWaves, kCellsWaves, maxr);
+  const size_t many = cells_lds_size<4, 9, false>(kCellsWaves, kCellsWaves, maxr);
+  return one > many ? one : many;
 }
 
-// Persistent workgroups (sixteen per CU) popping items:
-__global__ void __launch_bounds__(64) k_cells_batch(const GatherArgs* __restrict__ fields,
-                                                    const BatchSeg* __restrict__ segs,
-                                                    uint32_t* __restrict__ ctl, int maxr) {
-  extern __shared__ __align__(16) unsigned char s_dyn[];
+// One workgroup per item and part (blockIdx.y):
+template <bool kWide>
+__global__ void __launch_bounds__(256, 3) k_cells_items(const GatherArgs* __restrict__ fields,
+                                                     const BatchSeg* __restrict__ segs,
+                                                     uint32_t nseg) {
+  extern __shared__ __align__(32) unsigned char s_dyn[];
+  const uint32_t it = blockIdx.x;
+  const BatchSeg sg = batch_seg_of(segs, nseg, it);
+  const GatherArgs& a = fields[sg.field];
+  if (blockIdx.y > 0 && a.C == 1) return;
+  cells_item<kWide>(a, (int)(it - sg.base), (int)blockIdx.y, s_dyn);
+}
+
+// Persistent workgroups (four per CU) popping items:
+template <bool kWide>
+__global__ void __launch_bounds__(256, 3) k_cells_batch(const GatherArgs* __restrict__ fields,
+                                                     const BatchSeg* __restrict__ segs,
+                                                     uint32_t* __restrict__ ctl) {
+  extern __shared__ __align__(32) unsigned char s_dyn[];
   __shared__ uint32_t s_item;
-  const CellsLds L = cells_lds(s_dyn, maxr);
   const uint32_t total = ctl[8];
   const uint32_t nseg = ctl[9];
   const int home = (int)(blockIdx.x % kBatchXcds);
@@ -119,8 +139,13 @@ __global__ void __launch_bounds__(64) k_cells_batch(const GatherArgs* __restrict
     const uint32_t it = batch_next_item(ctl, total, home, &k, &s_item);
     if (it == 0xFFFFFFFFu) break;
     const BatchSeg sg = batch_seg_of(segs, nseg, it);
-    gather_cells_tile(fields[sg.field], (int)(it - sg.base), L);
-    __syncthreads();
+    const GatherArgs& a = fields[sg.field];
+    const int parts = a.C == 1 ? 1 : kCellsParts;
+#pragma nounroll
+    for (int part = 0; part < parts; ++part) {
+      cells_item<kWide>(a, (int)(it - sg.base), part, s_dyn);
+      __syncthreads();
+    }
   }
 }
 
@@ -235,12 +260,14 @@ hcg_status launch_class(int cls, int qw, bool wide, const GatherArgs* fields,
   }
   switch (cls) {
     case kClsCells: {
-      // one-wave workgroups; the persistent grid eight per 256-thread one
       const size_t lds = cells_batch_lds_bytes(l.cells_maxr);
-      if (l.strategy == kLaunchItems)
-        k_cells_items<<<l.nitems, 64, lds, stream>>>(fields, segs, l.nseg, l.cells_maxr);
-      else
-        k_cells_batch<<<l.nblocks * 8, 64, lds, stream>>>(fields, segs, ctl, l.cells_maxr);
+      if (l.strategy == kLaunchItems) {
+        if (wide) k_cells_items<true><<<dim3(l.nitems, kCellsParts), 256, lds, stream>>>(fields, segs, l.nseg);
+        else k_cells_items<false><<<dim3(l.nitems, kCellsParts), 256, lds, stream>>>(fields, segs, l.nseg);
+      } else {
+        if (wide) k_cells_batch<true><<<l.nblocks * 2, 256, lds, stream>>>(fields, segs, ctl);
+        else k_cells_batch<false><<<l.nblocks * 2, 256, lds, stream>>>(fields, segs, ctl);
+      }
       break;
     }
     case kBF16Split: launch_cls<kBF16Split>(1, wide, fields, segs, ctl, l, stream); break;
@@ -430,7 +457,8 @@ hcg_status build_items(hcg_batch_s* b, const hcg_field_data* data, int qw, int c
                                 : (uint64_t)sg.ntiles;
       base += span * sg.slabs;
       if (base >= 0x7FFFFFF0ull) return fail(HCG_E_UNSUPPORTED, "hcg_grid_batch: too many items");
-      wide = wide || !(b->h_fields[f].c2R < kNarrowChord2);
+      const GatherArgs& a = b->h_fields[f];
+      wide = wide || !(c == kClsCells ? cells_narrow(a.c2R, a.kern) : a.c2R < kNarrowChord2);
     }
     b->nitems[c] = (uint32_t)base;
     b->nseg[c] = nseg;

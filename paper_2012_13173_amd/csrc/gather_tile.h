@@ -1,7 +1,6 @@
 // Device code of the gather shared by the per-plan kernels (gather.hip) and
 // the persistent batch kernels (batch.hip): candidate staging, the weights
-// of Eq. (1) and the matrix-core contraction of one (tile, channel slab), and
-// the one-lane-per-cell accumulation of a tile for few channels.
+// of Eq. (1) and the matrix-core contraction of one (tile, channel slab).
 #pragma once
 
 #include "hcg_internal.h"
@@ -1210,86 +1209,6 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& a, int tile, int s
         }
       }
   }
-}
-
-// LDS of the few-channel gather in a batch (one wave per workgroup), carved
-// from dynamic LDS of cells_batch_lds_bytes(maxr) bytes with maxr the largest
-// range count of the batch's plans: small, so that many tiles are in flight
-// on a CU -- most tiles of a sparse field hold a few candidates, and their
-// time is the latency of the range, vector and value loads.
-struct CellsLds {
-  double4* xyz;       // [kKB]
-  float (*spec)[8];   // [kKB][8]
-  uint2* rng;         // [maxr]
-  uint32_t* pre;      // [maxr + 1]
-};
-__host__ __device__ constexpr size_t cells_batch_lds_bytes(int maxr) {
-  return sizeof(double4) * kKB + sizeof(float) * kKB * 8 + sizeof(uint2) * (size_t)maxr +
-         sizeof(uint32_t) * ((size_t)maxr + 1);
-}
-__device__ inline CellsLds cells_lds(unsigned char* base, int maxr) {
-  CellsLds L;
-  L.xyz = (double4*)base;
-  L.spec = (float (*)[8])(L.xyz + kKB);
-  L.rng = (uint2*)(L.spec + kKB);
-  L.pre = (uint32_t*)(L.rng + maxr);
-  return L;
-}
-
-// Few channels (C <= kCM <= 8) for a 64-thread workgroup: one lane per cell
-// of the 8 x 8 tile, candidates staged 64 at a time, weights and sums in
-// FP64 (the per-plan k_gather_cells without the split of the candidates).
-template <int kCM>
-__device__ inline void gather_cells_tile_wave(const GatherArgs& a, int tile, const CellsLds& sm) {
-  const int lane = threadIdx.x;
-  const int tx = tile % a.ntx, ty = tile / a.ntx;
-  const GridGeom& g = a.g;
-  const int ix = tx * kTileX + (lane & 7), iy = ty * kTileY + (lane >> 3);
-  const CellVec cell = cell_at(a.cells, g, ix, iy);
-  const uint32_t total =
-      stage_ranges(a.ranges + (int64_t)tile * a.maxr, a.nranges[tile], sm.rng, sm.pre);
-  const int C = (int)a.C;
-  const float* spec = (const float*)a.spec;
-  double acc[kCM];
-#pragma unroll
-  for (int c = 0; c < kCM; ++c) acc[c] = 0.0;
-  double wsum = 0.0;
-  uint32_t cur = 0;
-  for (uint32_t q0 = 0; q0 < total; q0 += kKB) {
-    const uint32_t q = q0 + lane;
-    if (q < total) {
-      const uint32_t pos = cand_pos(q, sm.rng, sm.pre, &cur);
-      sm.xyz[lane] = a.xyz[pos];
-      const int64_t row = a.perm[pos];
-#pragma unroll
-      for (int c = 0; c < kCM; ++c) sm.spec[lane][c] = (c < C) ? spec[row * C + c] : 0.f;
-    }
-    __syncthreads();
-    const int kmax = (int)min<uint32_t>(kKB, total - q0);
-    for (int k = 0; k < kmax; ++k) {
-      const double c2 = chord2(cell, sm.xyz[k]);
-      if (c2 <= a.c2R) {
-        const double w = pair_weight64(c2, a.kern.wscale);
-        wsum += w;
-#pragma unroll
-        for (int c = 0; c < kCM; ++c) acc[c] += w * (double)sm.spec[k][c];
-      }
-    }
-    __syncthreads();
-  }
-  if (ix >= g.nx || iy >= g.ny) return;
-  const int64_t G = (int64_t)g.nx * g.ny;
-  const int64_t cellidx = (int64_t)iy * g.nx + ix;
-  if (a.wmap) a.wmap[cellidx] = (float)wsum;
-#pragma unroll
-  for (int c = 0; c < kCM; ++c)
-    if (c < C) a.cube[c * G + cellidx] = (wsum != 0.0) ? (float)(acc[c] / wsum) : __builtin_nanf("");
-}
-
-// The few-channel gather of one tile, by channel count.
-__device__ inline void gather_cells_tile(const GatherArgs& a, int tile, const CellsLds& sm) {
-  if (a.C == 1) gather_cells_tile_wave<1>(a, tile, sm);
-  else gather_cells_tile_wave<8>(a, tile, sm);
 }
 
 }  // namespace hcg

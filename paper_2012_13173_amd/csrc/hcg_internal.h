@@ -265,6 +265,12 @@ constexpr double kNarrowChord2 = 1e-4;
 // at every synchronisation.  Lives until the process ends.
 hipMemPool_t plan_pool();
 
+// Few-channel gather of a plan (cells.hip): FP32 spectra, C <= 8; with mask a
+// non-finite value is a flag and wcube gets each channel's W.  may_alloc:
+// stream-ordered scratch may be taken (the same results without it, slower).
+hcg_status launch_cells(const hcg_plan_s* p, const float* spec, int C, float* cube, float* wmap,
+                        float* wcube, bool mask, bool may_alloc, hipStream_t stream);
+
 struct BatchSeg {
   uint32_t base, ntiles, slabs, field;
 };

@@ -101,12 +101,10 @@ __device__ __forceinline__ CellFrame cell_frame(const CellVec& c) {
 // exponential and sine: the elliptical Gaussian takes the sample's offset
 // (v - c) in the cell's tangent plane, whose direction is the bearing of the
 // great circle from the cell to the sample; the tapered sinc takes d alone.
-__device__ __forceinline__ double pair_weight_gen(const KernelParams& k, double c2,
-                                                  const double4& v, const CellVec& c,
-                                                  const CellFrame& f) {
+__device__ __forceinline__ double pair_weight_gen(const KernelParams& k, double c2, double dx,
+                                                  double dy, double dz, const CellFrame& f) {
   const double d2 = dist2_from_chord2<true>(c2);
   if (k.type == kElliptic) {
-    const double dx = v.x - c.x, dy = v.y - c.y, dz = v.z - c.z;
     const double xe = dx * f.ex + dy * f.ey;
     const double xn = dx * f.nx + dy * f.ny + dz * f.nz;
     const double a = xn * k.cpa + xe * k.spa, b = xe * k.cpa - xn * k.spa;
@@ -120,6 +118,11 @@ __device__ __forceinline__ double pair_weight_gen(const KernelParams& k, double 
     return sinc * exp2(d2 * k.taper_k);
   }
   return exp2(d2 * k.wscale);
+}
+__device__ __forceinline__ double pair_weight_gen(const KernelParams& k, double c2,
+                                                  const double4& v, const CellVec& c,
+                                                  const CellFrame& f) {
+  return pair_weight_gen(k, c2, v.x - c.x, v.y - c.y, v.z - c.z, f);
 }
 
 // Candidate search in one ring for cells spanning [lon_a, lon_b] x
@@ -202,5 +205,26 @@ inline double support_chord2(const hcg_plan_s* p) {
   return 4.0 * s * s;
 }
 inline double weight_scale(const hcg_plan_s* p) { return p->kern.wscale; }
+
+// Gather arguments of a plan (the form, its pointers and the outputs are the
+// caller's).
+inline GatherArgs plan_args(const hcg_plan_s* p) {
+  GatherArgs a;
+  memset(&a, 0, sizeof(a));
+  a.cells = p->cells;
+  a.kern = p->kern;
+  a.xyz = p->xyz;
+  a.sentinel = (uint32_t)p->n;
+  a.perm = p->perm;
+  a.ranges = p->ranges;
+  a.nranges = p->nranges;
+  a.maxr = p->maxr;
+  a.g = p->grid;
+  a.ntx = p->ntx;
+  a.ntiles = p->ntx * p->nty;
+  a.tiles_per_xcd = (a.ntiles + 7) / 8;
+  a.c2R = support_chord2(p);
+  return a;
+}
 
 }  // namespace hcg

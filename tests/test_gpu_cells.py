@@ -1,0 +1,62 @@
+"""The few-channel gather (FP32, C <= 8): every channel-count kernel, at the
+numbers of waves per sub-block of cells that the launch chooses from (one,
+four, and as many as a workgroup takes), with the values read through the
+permutation and put into the plan's order first, against the oracle on
+sampled cells: 1e-5 per channel, W to 1e-6 (the FP32 form's bounds; both
+sides sum in FP64 and differ by the rounding of the weights, 2.7e-7)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2012_13173_amd as hcg
+import synth
+from tests.gridcheck import (assert_cube_close, assert_weights_close, gather_cells, sample_cells,
+                             sampled_oracle)
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+# (n, C, nx, ny, cell', FWHM', support in sigma): ragged tiles; 2 tiles;
+# four waves a sub-block; one wave; n on both sides of the value sort's
+# threshold; cells wider than the support; a wide support (0.64 deg)
+CASES = [(400, 1, 9, 7, 1.0, 3.0, 3.0), (400, 8, 13, 3, 1.0, 3.0, 3.0),
+         (30_000, 2, 190, 141, 0.5, 3.0, 3.0), (30_000, 3, 150, 141, 0.5, 3.0, 3.0),
+         (262_143, 4, 170, 90, 0.5, 3.0, 3.0), (262_144, 4, 170, 90, 0.5, 3.0, 3.0),
+         (300_000, 1, 40, 33, 9.0, 3.0, 3.0), (270_000, 7, 390, 280, 0.5, 2.5, 5.0),
+         (20_000, 5, 33, 21, 10.0, 30.0, 3.0)]
+
+
+@pytest.mark.parametrize("n,nchan,nx,ny,cell,fwhm,sigmas", CASES)
+def test_few_channels_match_the_oracle(n, nchan, nx, ny, cell, fwhm, sigmas):
+    w = synth.small_cube(n=n, nchan=nchan, nx=nx, ny=ny, cell_arcmin=cell, fwhm_arcmin=fwhm,
+                         support_sigma=sigmas, seed=1700 + nchan + nx)
+    plan = hcg.hcg_plan(w.lon.to(DEV), w.lat.to(DEV), w.grid, w.fwhm_deg, w.support_deg)
+    spec = w.spectra.to(DEV).contiguous()
+    shape = (nchan, ny, nx)
+    maps = []
+    for grid in (hcg.hcg_grid, hcg.hcg_grid_noalloc):
+        cube = torch.full(shape, 12345.0, dtype=torch.float32, device=DEV)
+        W = torch.full(shape[1:], -1.0, dtype=torch.float32, device=DEV)
+        print(f"{grid.__name__} n={n} C={nchan} {nx}x{ny}", flush=True)
+        grid(plan, spec, cube, W)
+        torch.cuda.synchronize()
+        maps.append((cube, W))
+    (cube, W), (cube_b, W_b) = maps
+    # the values' order in memory does not reach the sums
+    assert torch.equal(cube.view(torch.int32), cube_b.view(torch.int32))
+    assert torch.equal(W.view(torch.int32), W_b.view(torch.int32))
+    groups = sample_cells(w.grid, seed=5, patches=4, patch=min(6, ny))
+    cells = np.concatenate(groups)
+    ref = [sampled_oracle(w, c) for c in groups]
+    V, Wg = gather_cells(cube, W, cells)
+    assert_cube_close(V.T, np.concatenate([v for v, _ in ref]).T, 1e-5, f"C={nchan} {nx}x{ny}")
+    assert_weights_close(Wg, np.concatenate([x for _, x in ref]))
+    # flags: none set, so each channel's W is the map's and V is unchanged to
+    # the last place (the same sums in the same order)
+    cube_m = torch.empty_like(cube)
+    W_m = torch.empty_like(cube)
+    hcg.hcg_grid_masked(plan, spec, cube_m, W_m)
+    torch.cuda.synchronize()
+    torch.testing.assert_close(cube_m, cube, rtol=2e-7, atol=0, equal_nan=True)
+    torch.testing.assert_close(W_m, W[None].expand_as(W_m), rtol=2e-7, atol=0)
+    plan.destroy()
