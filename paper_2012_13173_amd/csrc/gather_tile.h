@@ -1195,7 +1195,7 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& a, int tile, int s
           }
         }
         float* dst = a.cube + ch * G + row0;
-        float* wdst = kMask ? a.wcube + ch * G + row0 : nullptr;
+        float* wdst = kMask && a.wcube ? a.wcube + ch * G + row0 : nullptr;
         if (full) {
           *(floatx4*)dst = floatx4{v[0], v[1], v[2], v[3]};
           if (kMask && wdst) *(floatx4*)wdst = floatx4{wc[0], wc[1], wc[2], wc[3]};
