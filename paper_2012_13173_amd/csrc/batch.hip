@@ -25,6 +25,7 @@
 #include <string>
 #include <vector>
 
+#include "batch_items.h"
 #include "cells_tile.h"
 #include "forms.h"
 #include "gather_tile.h"
@@ -39,54 +40,16 @@ namespace hcg {
 // registers of two workgroups per CU.
 constexpr int kClsCells = 6;
 constexpr int kClsScalarRows = 7;
-constexpr int kClasses = 13;
-
-// ctl: [0..7] next item of each XCD's segment, [8] item count, [9] segment
-// count.  The item space of a class is cut into eight contiguous segments,
-// one per XCD (the hardware deals workgroups to the XCDs in turn, so
-// workgroup b starts on XCD b % 8); a workgroup pops items from its own
-// XCD's segment -- neighbouring tiles of one field, sharing candidate rows in
-// that XCD's L2 -- and, once it is empty, from the others.
-__device__ __forceinline__ uint32_t batch_seg_begin(uint32_t total, int x) {
-  return (uint32_t)(((uint64_t)total * (uint32_t)x) / kBatchXcds);
-}
+// FP32 by independent waves (gather_wave.hip), 64 or 128 channels to a wave,
+// rows read four channels or one at a time.
+constexpr int kClsWave = 13;
+constexpr int kClasses = 17;
+constexpr int wave_cls(int j, bool vec) { return kClsWave + (j == 8 ? 1 : 0) + (vec ? 0 : 2); }
+constexpr int wave_cls_j(int cls) { return (cls - kClsWave) & 1 ? 8 : 4; }
 
 __global__ void k_batch_reset(uint32_t* __restrict__ ctl) {
   const uint32_t total = ctl[8];
   for (int x = 0; x < kBatchXcds; ++x) ctl[x] = batch_seg_begin(total, x);
-}
-
-// The next item of a persistent workgroup: thread 0 pops one from its
-// XCD's segment, then from the others once it is empty (*k counts the
-// segments it has found empty); 0xFFFFFFFF when every segment is empty.
-// Called by every thread of the workgroup.
-__device__ inline uint32_t batch_next_item(uint32_t* __restrict__ ctl, uint32_t total, int home,
-                                           int* k, uint32_t* s_item) {
-  if (threadIdx.x == 0) {
-    uint32_t it = 0xFFFFFFFFu;
-    while (*k < kBatchXcds) {
-      const int x = (home + *k) % kBatchXcds;
-      const uint32_t i = atomicAdd(&ctl[x], 1u);
-      if (i < batch_seg_begin(total, x + 1)) { it = i; break; }
-      ++*k;
-    }
-    *s_item = it;
-  }
-  __syncthreads();
-  const uint32_t it = __builtin_amdgcn_readfirstlane(*s_item);
-  __syncthreads();
-  return it;
-}
-
-// The segment of item it: the last one whose base is <= it.
-__device__ inline BatchSeg batch_seg_of(const BatchSeg* __restrict__ segs, uint32_t nseg,
-                                        uint32_t it) {
-  uint32_t lo = 0, hi = nseg - 1;
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi + 1) >> 1;
-    if (segs[mid].base <= it) lo = mid; else hi = mid - 1;
-  }
-  return segs[lo];
 }
 
 // The few-channel class (FP32, C <= 8): four waves per tile, one sub-block
@@ -270,6 +233,11 @@ hcg_status launch_class(int cls, int qw, bool wide, const GatherArgs* fields,
       }
       break;
     }
+    case kClsWave: case kClsWave + 1: case kClsWave + 2: case kClsWave + 3:
+      launch_wave_items(wave_cls_j(cls), cls < kClsWave + 2, wide, l.strategy == kLaunchItems,
+                        l.strategy == kLaunchItems ? l.nitems : (uint32_t)l.nblocks * 2u, fields,
+                        segs, l.nseg, ctl, l.cells_maxr, stream);
+      break;
     case kBF16Split: launch_cls<kBF16Split>(1, wide, fields, segs, ctl, l, stream); break;
     case kF32: launch_cls<kF32>(qw, wide, fields, segs, ctl, l, stream); break;
     case kBF16: launch_cls<kBF16>(qw, wide, fields, segs, ctl, l, stream); break;
@@ -288,8 +256,10 @@ hcg_status launch_class(int cls, int qw, bool wide, const GatherArgs* fields,
 }
 
 // Kernel class of a field's data (vec: rows read four elements at a time).
-int field_class(const hcg_field_data& d, bool vec) {
+int field_class(const hcg_plan_s* p, const hcg_field_data& d, bool vec) {
   if (d.dtype == HCG_F32 && d.nchan <= 8) return kClsCells;
+  if (d.dtype == HCG_F32 && f32_kernel(p, d.nchan) == F32Kernel::kWave)
+    return wave_cls(d.nchan <= 64 ? 4 : 8, vec);
   return vec ? (int)d.dtype : kClsScalarRows + (int)d.dtype;
 }
 
@@ -425,7 +395,7 @@ hcg_status build_items(hcg_batch_s* b, const hcg_field_data* data, int qw, int c
     const int64_t C = data[f].nchan;
     const int cls = b->built_cls[f];
     const bool cells = cls == kClsCells;
-    const int64_t width = cells ? C : 256 * b->cls_qw[cls];
+    const int64_t width = cells ? C : cls >= kClsWave ? 16 * wave_cls_j(cls) : 256 * b->cls_qw[cls];
     const int64_t slabs = cells ? 1 : (C + width - 1) / width;
     const std::vector<uint32_t>& nc = b->ncand[f];
     double cand = 0.0;
@@ -433,7 +403,7 @@ hcg_status build_items(hcg_batch_s* b, const hcg_field_data* data, int qw, int c
     // candidates x channels, plus the output writes
     cost[f] = cand * (cells ? 8.0 : (double)std::max<int64_t>(C, 64)) +
               64.0 * (double)nc.size() * (double)C;
-    seg[f] = BatchSeg{0u, (uint32_t)nc.size(), (uint32_t)slabs, (uint32_t)f};
+    seg[f] = BatchSeg{0u, (uint32_t)b->h_fields[f].ntiles, (uint32_t)slabs, (uint32_t)f};
   }
   std::vector<size_t> order(nf);
   for (size_t f = 0; f < nf; ++f) order[f] = f;
@@ -637,7 +607,17 @@ extern "C" hcg_status hcg_grid_batch(hcg_batch_t batch, const hcg_field_data* da
     const hcg_field_data& d = data[f];
     fresh[f] = make_field_args(b->plans[f], d);
     vecs[f] = fresh[f].vec;
-    clss[f] = field_class(d, vecs[f] != 0);
+    clss[f] = field_class(b->plans[f], d, vecs[f] != 0);
+    if (clss[f] >= kClsWave) {
+      // the same waves to a cell block as hcg_grid takes (the same sums); with
+      // several, an item is a cell block
+      GatherArgs& a = fresh[f];
+      a.vec = wave_shape(b->plans[f], d.nchan, vecs[f] != 0, false).nk;
+      if (a.vec > 1) a.ntiles *= 4;
+      a.tiles_per_xcd = (a.ntiles + 7) / 8;
+      a.kern.kmaj = a.kern.wscale * (1.0 / 12.0);
+      a.kern.kmin = a.kern.wscale * (1.0 / 90.0);
+    }
     if (!layout_changed && (b->built_C[f] != d.nchan || b->built_vec[f] != vecs[f] ||
                             b->built_cls[f] != clss[f]))
       layout_changed = true;

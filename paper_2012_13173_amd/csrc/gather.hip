@@ -78,11 +78,28 @@ __global__ void __launch_bounds__(64) k_count_pairs(const GatherArgs a,
 // over) a gather takes 256-channel slabs.
 constexpr int64_t kFewGroups = 1024;
 
+// Which gather an FP32 map of more than 8 channels takes.  (Times in us of
+// tiles / independent waves; 0.5' cells and FWHM 3' unless said.)
+//   - Independent waves read a row once per cell block it reaches, up to 19
+//     times, and keep all of their matrix work: up to 128 channels, or where
+//     the spectra stay in the caches.  2M samples x 64 -> 400 x 400: 2549 /
+//     1363; x 128: 3174 / 2589; x 256: 3858 / 4960; 20,000 x 1024 -> 400 x 400
+//     of 1.2': 500 / 327, 100,000: 628 / 591, 500,000: 1585 / 1778.  Flagged,
+//     2M x 64: 5790 / 2385; x 256: 7525 / 8442.
+F32Kernel f32_kernel(const hcg_plan_s* p, int64_t C) {
+  const bool cached = (double)p->n * (double)C * 4.0 <= 100e6;
+  return C <= 128 || cached ? F32Kernel::kWave : F32Kernel::kTile;
+}
+
 template <int kForm, bool kPacked = false, bool kMask = false>
 static hcg_status launch_mfma(const hcg_plan_s* p, const void* spec, const void* spec_lo,
                               const float* scale, int64_t C, float* cube, float* wmap,
                               hipStream_t stream, float* wcube = nullptr) {
   static_assert(!(kPacked && kForm == kF32), "plan-ordered spectra are a low-precision input");
+  if constexpr (kForm == kF32) {
+    if (f32_kernel(p, C) == F32Kernel::kWave)
+      return launch_wave(p, (const float*)spec, C, cube, wmap, wcube, kMask, stream);
+  }
   GatherArgs a = plan_args(p);
   a.wcube = wcube;
   a.spec = spec;
@@ -92,11 +109,11 @@ static hcg_status launch_mfma(const hcg_plan_s* p, const void* spec, const void*
   a.cube = cube;
   a.wmap = wmap;
   const size_t esz = (kForm == kF32) ? 4 : is_fp8(kForm) ? 1 : 2;
+  if (kPacked && ((uintptr_t)spec % (8 * esz) != 0 || (uintptr_t)spec_lo % (8 * esz) != 0))
+    return fail(HCG_E_ARG, "hcg_grid_packed: spectra must be %zu-byte aligned", 8 * esz);
   // plan-ordered spectra are read 8 samples of a channel at a time
   const bool vec = kPacked || ((C % 4 == 0) && ((uintptr_t)spec % (4 * esz) == 0) &&
                                (!spec_lo || (uintptr_t)spec_lo % (4 * esz) == 0));
-  if (kPacked && ((uintptr_t)spec % (8 * esz) != 0 || (uintptr_t)spec_lo % (8 * esz) != 0))
-    return fail(HCG_E_ARG, "hcg_grid_packed: spectra must be %zu-byte aligned", 8 * esz);
   a.vec = vec ? 1 : 0;
   // 512-channel slabs (weights computed once per 512 channels) where the
   // registers allow it, else 256; a map of few tiles takes 256-channel slabs

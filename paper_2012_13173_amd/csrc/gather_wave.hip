@@ -1,0 +1,163 @@
+// Launches of the independent-wave gather (gather_wave.h) on one plan.
+#include <cmath>
+
+#include "batch_items.h"
+#include "gather_wave.h"
+
+namespace hcg {
+
+// Waves per SIMD that a kernel's registers are held to.
+template <int kJ, bool kMask, bool kGen>
+constexpr int kWaveOccupancy = kGen || kJ == 16 ? 2 : kJ * (kMask ? 2 : 1) <= 4 ? 3 : 2;
+
+template <int kJ, bool kVec, bool kMask, bool kWide, bool kGen>
+__global__ void __launch_bounds__(256, (kWaveOccupancy<kJ, kMask, kGen>)) k_gather_wave(const GatherArgs a, int subs, int nk) {
+  extern __shared__ __align__(16) unsigned char s_dyn[];
+  // one slab after the other; within one, the XCDs (workgroups go to them in
+  // turn) take contiguous eighths of the cell blocks
+  const int per_tile = 4 / subs;
+  const int64_t work = (int64_t)a.ntiles * per_tile, eighth = (work + 7) / 8;
+  const int64_t slab = blockIdx.x / (8 * eighth), b = blockIdx.x - slab * 8 * eighth;
+  const int64_t w = (b & 7) * eighth + (b >> 3);
+  if (w >= work) return;
+  const int tile = (int)(w / per_tile);
+  gather_wave<kJ, kVec, kMask, kWide, kGen>(a, tile, (int)slab, (int)(w - (int64_t)tile * per_tile) * subs,
+                                            subs, nk, s_dyn);
+}
+
+template <int kJ, bool kVec, bool kMask, bool kWide, bool kGen>
+static hcg_status launch(const GatherArgs& a, int nk, hipStream_t stream) {
+  const int subs = nk > 1 ? 1 : 4;
+  const int64_t work = (int64_t)a.ntiles * (4 / subs);
+  const int64_t blocks = (work + 7) / 8 * 8 * ((a.C + 16 * kJ - 1) / (16 * kJ));
+  if (blocks > INT32_MAX) return fail(HCG_E_UNSUPPORTED, "hcg_grid: too many channels");
+  const size_t lds = wave_lds_bytes<kJ, kMask>(subs * nk, nk, a.maxr);
+  k_gather_wave<kJ, kVec, kMask, kWide, kGen>
+      <<<(unsigned)blocks, 64 * subs * nk, lds, stream>>>(a, subs, nk);
+  HCG_LAUNCH_CHECK("k_gather_wave");
+  return HCG_OK;
+}
+
+template <bool kVec, bool kMask, bool kWide, bool kGen>
+static hcg_status launch_j(const GatherArgs& a, int j, int nk, hipStream_t stream) {
+  if (j == 4) return launch<4, kVec, kMask, kWide, kGen>(a, nk, stream);
+  // (rows read one channel at a time: sixteen loads of a row would spill)
+  if constexpr (!kMask && kVec)
+    if (j == 16) return launch<16, kVec, kMask, kWide, kGen>(a, nk, stream);
+  return launch<8, kVec, kMask, kWide, kGen>(a, nk, stream);
+}
+
+hcg_status launch_wave(const hcg_plan_s* p, const float* spec, int64_t C, float* cube, float* wmap,
+                       float* wcube, bool mask, hipStream_t stream) {
+  GatherArgs a = plan_args(p);
+  if (p->kern.type == kGauss) {  // the series factors, in fields a Gaussian leaves unused
+    a.kern.kmaj = a.kern.wscale * (1.0 / 12.0);
+    a.kern.kmin = a.kern.wscale * (1.0 / 90.0);
+  }
+  a.spec = spec;
+  a.C = C;
+  a.cube = cube;
+  a.wmap = wmap;
+  a.wcube = wcube;
+  const bool vec = C % 4 == 0 && (uintptr_t)spec % 16 == 0;
+  const bool gen = p->kern.type != kGauss, wide = !(a.c2R < kNarrowChord2);
+  const WaveShape sh = wave_shape(p, C, vec, mask);
+#define HCG_WAVE(MASK, WIDE, GEN)                                       \
+  (vec ? launch_j<true, MASK, WIDE, GEN>(a, sh.j, sh.nk, stream)         \
+       : launch_j<false, MASK, WIDE, GEN>(a, sh.j, sh.nk, stream))
+  if (mask) return gen ? HCG_WAVE(true, true, true) : HCG_WAVE(true, true, false);
+  if (gen) return HCG_WAVE(false, true, true);
+  return wide ? HCG_WAVE(false, true, false) : HCG_WAVE(false, false, false);
+#undef HCG_WAVE
+}
+
+// Channels of a wave and waves of a cell block.  Wide slabs compute the
+// weights less often; a map of few cell blocks takes narrower ones, then
+// several waves to a cell block, until there are kWaveFew waves (four per SIMD:
+// 20,000 samples x 67 channels -> 45 x 37, 120 cell blocks: 335 us with one
+// workgroup per 8 x 8 tile, 42 us so).
+constexpr int64_t kWaveFew = 4096;
+WaveShape wave_shape(const hcg_plan_s* p, int64_t C, bool vec, bool mask) {
+  const int64_t blocks = 4 * (int64_t)p->ntx * p->nty;
+  int j = C <= 64 ? 4 : C <= 128 || mask || !vec ? 8 : 16;
+  while (j > 4 && blocks * ((C + 16 * j - 1) / (16 * j)) < kWaveFew) j /= 2;
+  const int nk = blocks * ((C + 16 * j - 1) / (16 * j)) < kWaveFew ? 4 : 1;
+  return WaveShape{j, nk};
+}
+
+// ---------------------------------------------------------------------------
+// Fields of a batch.  A unit is a tile, or with several waves to a cell block a
+// cell block; a workgroup of four waves takes one unit of one channel slab.
+// ---------------------------------------------------------------------------
+template <int kJ, bool kVec, bool kWide>
+__device__ inline void wave_unit(const GatherArgs& a, uint32_t unit, uint32_t slab,
+                                 unsigned char* lds) {
+  const int nk = a.vec;
+  if (nk > 1)
+    gather_wave<kJ, kVec, false, kWide, false>(a, (int)(unit >> 2), (int)slab, (int)(unit & 3u), 1,
+                                               nk, lds);
+  else
+    gather_wave<kJ, kVec, false, kWide, false>(a, (int)unit, (int)slab, 0, 4, 1, lds);
+}
+
+template <int kJ, bool kVec, bool kWide>
+__global__ void __launch_bounds__(256, 2) k_wave_items(const GatherArgs* __restrict__ fields,
+                                                       const BatchSeg* __restrict__ segs,
+                                                       uint32_t nseg) {
+  extern __shared__ __align__(16) unsigned char s_dyn[];
+  const uint32_t it = blockIdx.x;
+  const BatchSeg sg = batch_seg_of(segs, nseg, it);
+  const uint32_t local = it - sg.base;
+  const GatherArgs& a = fields[sg.field];
+  const uint32_t per_slab = (uint32_t)a.tiles_per_xcd * 8u;
+  const uint32_t slab = local / per_slab, loc = local - slab * per_slab;
+  const uint32_t unit = (loc & 7u) * (uint32_t)a.tiles_per_xcd + (loc >> 3);
+  if (unit < (uint32_t)a.ntiles) wave_unit<kJ, kVec, kWide>(a, unit, slab, s_dyn);
+}
+
+template <int kJ, bool kVec, bool kWide>
+__global__ void __launch_bounds__(256, 2) k_wave_batch(const GatherArgs* __restrict__ fields,
+                                                       const BatchSeg* __restrict__ segs,
+                                                       uint32_t* __restrict__ ctl) {
+  extern __shared__ __align__(16) unsigned char s_dyn[];
+  __shared__ uint32_t s_item;
+  const uint32_t total = ctl[8], nseg = ctl[9];
+  const int home = (int)(blockIdx.x % kBatchXcds);
+  int k = 0;
+  for (;;) {
+    const uint32_t it = batch_next_item(ctl, total, home, &k, &s_item);
+    if (it == 0xFFFFFFFFu) break;
+    const BatchSeg sg = batch_seg_of(segs, nseg, it);
+    const uint32_t local = it - sg.base, slab = local / sg.ntiles;
+    wave_unit<kJ, kVec, kWide>(fields[sg.field], local - slab * sg.ntiles, slab, s_dyn);
+    __syncthreads();
+  }
+}
+
+void launch_wave_items(int j, bool vec, bool wide, bool items, uint32_t blocks,
+                       const GatherArgs* fields, const BatchSeg* segs, uint32_t nseg,
+                       uint32_t* ctl, int maxr, hipStream_t stream) {
+#define HCG_ITEMS(J, VEC, WIDE)                                                                   \
+  do {                                                                                            \
+    const size_t a = wave_lds_bytes<J, false>(4, 1, maxr), b = wave_lds_bytes<J, false>(4, 4, maxr); \
+    const size_t lds = a > b ? a : b;                                                             \
+    if (items) k_wave_items<J, VEC, WIDE><<<blocks, 256, lds, stream>>>(fields, segs, nseg);      \
+    else k_wave_batch<J, VEC, WIDE><<<blocks, 256, lds, stream>>>(fields, segs, ctl);             \
+  } while (0)
+#define HCG_ITEMS_W(J, VEC)             \
+  do {                                  \
+    if (wide) HCG_ITEMS(J, VEC, true);  \
+    else HCG_ITEMS(J, VEC, false);      \
+  } while (0)
+  if (j == 4) {
+    if (vec) HCG_ITEMS_W(4, true);
+    else HCG_ITEMS_W(4, false);
+  } else {
+    if (vec) HCG_ITEMS_W(8, true);
+    else HCG_ITEMS_W(8, false);
+  }
+#undef HCG_ITEMS_W
+#undef HCG_ITEMS
+}
+
+}  // namespace hcg

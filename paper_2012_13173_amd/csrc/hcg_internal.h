@@ -265,17 +265,39 @@ constexpr double kNarrowChord2 = 1e-4;
 // at every synchronisation.  Lives until the process ends.
 hipMemPool_t plan_pool();
 
+struct BatchSeg {
+  uint32_t base, ntiles, slabs, field;
+};
+constexpr int kBatchXcds = 8;
+constexpr int kBatchCtl = 16;
+
+// Gathers of FP32 spectra of more than 8 channels, by what a map and channel
+// count are faster with (f32_kernel, gather.hip): 8 x 8 tiles shared by a
+// workgroup (gather_tile.h), independent waves (gather_wave.h).
+enum class F32Kernel { kTile, kWave };
+F32Kernel f32_kernel(const hcg_plan_s* p, int64_t C);
+
+// Independent waves (gather_wave.hip): any kernel shape, flagged or not.
+// wave_shape: 16-channel tiles of a wave and waves of a cell block, for a plan
+// and channel count (vec: rows read four channels at a time).
+struct WaveShape {
+  int j, nk;
+};
+WaveShape wave_shape(const hcg_plan_s* p, int64_t C, bool vec, bool mask);
+hcg_status launch_wave(const hcg_plan_s* p, const float* spec, int64_t C, float* cube, float* wmap,
+                       float* wcube, bool mask, hipStream_t stream);
+// The same for a batch's fields (vec of a field's arguments: its waves of a
+// cell block): one workgroup per item, or `blocks` persistent ones.
+void launch_wave_items(int j, bool vec, bool wide, bool items, uint32_t blocks,
+                       const GatherArgs* fields, const BatchSeg* segs, uint32_t nseg,
+                       uint32_t* ctl, int maxr, hipStream_t stream);
+
 // Few-channel gather of a plan (cells.hip): FP32 spectra, C <= 8; with mask a
 // non-finite value is a flag and wcube gets each channel's W.  may_alloc:
 // stream-ordered scratch may be taken (the same results without it, slower).
 hcg_status launch_cells(const hcg_plan_s* p, const float* spec, int C, float* cube, float* wmap,
                         float* wcube, bool mask, bool may_alloc, hipStream_t stream);
 
-struct BatchSeg {
-  uint32_t base, ntiles, slabs, field;
-};
-constexpr int kBatchXcds = 8;
-constexpr int kBatchCtl = 16;
 hcg_status plan_build_fields(int32_t nf, const hcg_field_desc* fd, const hcg_opts* opts,
                              hipStream_t stream, hcg_plan_t* plans, void** arena_out,
                              std::vector<std::vector<uint32_t>>* ncand, int32_t* failed);

@@ -1,15 +1,84 @@
-"""The gathers of FP32 maps of more than 8 channels at the edges of their
-ranges.  The few-channel gather (FP64 sums) stands in for the oracle: 1e-5 per
-channel, W of the flagged form (FP32 sums) to 1e-5."""
+"""The independent waves that FP32 maps of more than 8 channels take besides
+the 8 x 8-cell tiles, at the edges of their ranges: channel groups of 64, 128
+and 256 cut short, rows read four channels or one at a time, one or four waves
+to a cell block, flags.
+Bounds against the FP64 oracle are the FP32 form's: 1e-5 per channel, W to
+1e-6 (1e-5 for the flagged form's FP32 weight sums); the few-channel gather
+(FP64 sums) is held to the same bound where it stands in for the oracle."""
+import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2012_13173_amd as hcg
 import synth
-from tests.gridcheck import assert_cube_close, assert_weights_close
+from tests.gridcheck import (assert_cube_close, assert_weights_close, sample_cells)
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
+
+
+def _device_rows(spec, shift):
+    """Contiguous device rows that start `shift` floats past an aligned address."""
+    buf = torch.empty(spec.numel() + shift, dtype=torch.float32, device=DEV)
+    rows = buf[shift:].view(spec.shape)
+    rows.copy_(spec)
+    return rows
+
+
+def _flagged(spec, seed):
+    g = np.random.default_rng(seed)
+    s = spec.numpy().copy()
+    m = g.random(s.shape) < 0.05
+    s[m] = g.choice([np.nan, np.inf, -np.inf], size=int(m.sum()))
+    return torch.from_numpy(s)
+
+
+def _cells_lonlat(g, cells):
+    iy, ix = np.divmod(cells, g.nx)
+    return (g.lon0 + (ix - (g.nx - 1) / 2) * g.dlon, g.lat0 + (iy - (g.ny - 1) / 2) * g.dlat)
+
+
+# (n, C, nx, ny, cell', FWHM', floats past an aligned address)
+WAVE = [(300, 9, 5, 3, 1.0, 3.0, 0), (4000, 16, 21, 14, 1.0, 3.0, 0),
+        (4000, 64, 21, 14, 1.0, 3.0, 1), (9000, 65, 33, 17, 0.8, 3.0, 0),
+        (30_000, 64, 270, 259, 0.8, 3.0, 0), (30_000, 61, 270, 259, 0.8, 3.0, 0),
+        (30_000, 128, 270, 262, 0.8, 3.0, 0), (9000, 129, 33, 17, 0.8, 3.0, 0),
+        (20_000, 516, 190, 175, 1.2, 3.0, 0), (20_000, 260, 270, 250, 1.2, 3.0, 2),
+        (6000, 72, 25, 26, 8.0, 30.0, 0)]
+
+
+@pytest.mark.parametrize("n,nchan,nx,ny,cell,fwhm,shift", WAVE)
+@pytest.mark.parametrize("flags", [False, True])
+def test_independent_waves_match_the_oracle(n, nchan, nx, ny, cell, fwhm, shift, flags):
+    w = synth.small_cube(n=n, nchan=nchan, nx=nx, ny=ny, cell_arcmin=cell, fwhm_arcmin=fwhm,
+                         seed=2600 + nchan + nx)
+    spec = _flagged(w.spectra, 2601) if flags else w.spectra
+    plan = hcg.hcg_plan(w.lon.to(DEV), w.lat.to(DEV), w.grid, w.fwhm_deg, w.support_deg)
+    rows = _device_rows(spec, shift)
+    cube = torch.full((nchan, ny, nx), 12345.0, device=DEV)
+    W = torch.full((nchan, ny, nx) if flags else (ny, nx), -1.0, device=DEV)
+    print(f"waves n={n} C={nchan} {nx}x{ny} flags={flags}", flush=True)
+    if flags:
+        hcg.hcg_grid_masked(plan, rows, cube, W)
+        bare = torch.full_like(cube, 54321.0)
+        hcg.hcg_grid_masked(plan, rows, bare, None)  # without the channels' weights
+        torch.cuda.synchronize()
+        assert torch.equal(cube.view(torch.int32), bare.view(torch.int32))
+    else:
+        hcg.hcg_grid(plan, rows, cube, W)
+        torch.cuda.synchronize()
+    cells = np.concatenate(sample_cells(w.grid, seed=5, patches=4, patch=min(6, ny, nx)))
+    cl, cb = _cells_lonlat(w.grid, cells)
+    V, Wr, _ = oracle.grid_points(w.lon.numpy(), w.lat.numpy(), spec.numpy(), cl, cb,
+                                  w.support_deg, oracle.Kernel.gauss(w.fwhm_deg), masked=flags)
+    idx = torch.from_numpy(cells).to(DEV)
+    Vg = cube.reshape(nchan, -1)[:, idx].cpu().numpy()
+    Wg = W.reshape(-1, nx * ny)[:, idx].cpu().numpy()
+    assert_cube_close(Vg, V.T, 1e-5, f"C={nchan} {nx}x{ny}")
+    assert_weights_close(Wg, np.asarray(Wr).T if flags else np.asarray(Wr)[None],
+                         rtol=1e-5 if flags else 1e-6)
+    plan.destroy()
 
 
 @pytest.mark.parametrize("n,nchan", [(20_000, 12), (2_000_000, 129)])
