@@ -11,7 +11,7 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
-SOURCES = ["gather.hip", "batch.hip", "cells.hip", "gather_wave.hip",
+SOURCES = ["gather.hip", "batch.hip", "cells.hip", "gather_block.hip", "gather_wave.hip",
            "plan.hip", "quant.hip", "capi.hip", "stream.hip",
            "rowthreads.hip", "wcs.hip"]
 LIB = os.path.join(PKG, "libhcg.so")

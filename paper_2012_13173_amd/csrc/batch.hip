@@ -43,7 +43,10 @@ constexpr int kClsScalarRows = 7;
 // FP32 by independent waves (gather_wave.hip), 64 or 128 channels to a wave,
 // rows read four channels or one at a time.
 constexpr int kClsWave = 13;
-constexpr int kClasses = 17;
+// FP32 by blocks of 16 x 16 cells (gather_block.hip), rows read two channels
+// or one at a time.
+constexpr int kClsBlock = 17;
+constexpr int kClasses = 19;
 constexpr int wave_cls(int j, bool vec) { return kClsWave + (j == 8 ? 1 : 0) + (vec ? 0 : 2); }
 constexpr int wave_cls_j(int cls) { return (cls - kClsWave) & 1 ? 8 : 4; }
 
@@ -238,6 +241,11 @@ hcg_status launch_class(int cls, int qw, bool wide, const GatherArgs* fields,
                         l.strategy == kLaunchItems ? l.nitems : (uint32_t)l.nblocks * 2u, fields,
                         segs, l.nseg, ctl, l.cells_maxr, stream);
       break;
+    case kClsBlock: case kClsBlock + 1:
+      launch_block_items(cls == kClsBlock, l.strategy == kLaunchItems,
+                         l.strategy == kLaunchItems ? l.nitems : (uint32_t)l.nblocks / 2u, fields,
+                         segs, l.nseg, ctl, stream);
+      break;
     case kBF16Split: launch_cls<kBF16Split>(1, wide, fields, segs, ctl, l, stream); break;
     case kF32: launch_cls<kF32>(qw, wide, fields, segs, ctl, l, stream); break;
     case kBF16: launch_cls<kBF16>(qw, wide, fields, segs, ctl, l, stream); break;
@@ -258,8 +266,11 @@ hcg_status launch_class(int cls, int qw, bool wide, const GatherArgs* fields,
 // Kernel class of a field's data (vec: rows read four elements at a time).
 int field_class(const hcg_plan_s* p, const hcg_field_data& d, bool vec) {
   if (d.dtype == HCG_F32 && d.nchan <= 8) return kClsCells;
-  if (d.dtype == HCG_F32 && f32_kernel(p, d.nchan) == F32Kernel::kWave)
-    return wave_cls(d.nchan <= 64 ? 4 : 8, vec);
+  if (d.dtype == HCG_F32) {
+    const F32Kernel k = f32_kernel(p, d.nchan, false);
+    if (k == F32Kernel::kWave) return wave_cls(d.nchan <= 64 ? 4 : 8, vec);
+    if (k == F32Kernel::kBlock) return kClsBlock + (block_rows2(d.spectra, d.nchan) ? 0 : 1);
+  }
   return vec ? (int)d.dtype : kClsScalarRows + (int)d.dtype;
 }
 
@@ -395,7 +406,8 @@ hcg_status build_items(hcg_batch_s* b, const hcg_field_data* data, int qw, int c
     const int64_t C = data[f].nchan;
     const int cls = b->built_cls[f];
     const bool cells = cls == kClsCells;
-    const int64_t width = cells ? C : cls >= kClsWave ? 16 * wave_cls_j(cls) : 256 * b->cls_qw[cls];
+    const int64_t width = cells ? C : cls >= kClsBlock ? kBlockSlab
+                                  : cls >= kClsWave ? 16 * wave_cls_j(cls) : 256 * b->cls_qw[cls];
     const int64_t slabs = cells ? 1 : (C + width - 1) / width;
     const std::vector<uint32_t>& nc = b->ncand[f];
     double cand = 0.0;
@@ -608,7 +620,9 @@ extern "C" hcg_status hcg_grid_batch(hcg_batch_t batch, const hcg_field_data* da
     fresh[f] = make_field_args(b->plans[f], d);
     vecs[f] = fresh[f].vec;
     clss[f] = field_class(b->plans[f], d, vecs[f] != 0);
-    if (clss[f] >= kClsWave) {
+    if (clss[f] >= kClsBlock) {
+      block_args(b->plans[f], &fresh[f]);
+    } else if (clss[f] >= kClsWave) {
       // the same waves to a cell block as hcg_grid takes (the same sums); with
       // several, an item is a cell block
       GatherArgs& a = fresh[f];

@@ -77,17 +77,39 @@ __global__ void __launch_bounds__(64) k_count_pairs(const GatherArgs a,
 // Below this many 512-channel workgroups (two per CU on 256 CUs, twice
 // over) a gather takes 256-channel slabs.
 constexpr int64_t kFewGroups = 1024;
+// Fewest workgroups of the block gather (one per CU, two rounds).
+constexpr int64_t kFewBlocks = 512;
+
 
 // Which gather an FP32 map of more than 8 channels takes.  (Times in us of
-// tiles / independent waves; 0.5' cells and FWHM 3' unless said.)
+// tiles / independent waves / blocks; 0.5' cells and FWHM 3' unless said.)
 //   - Independent waves read a row once per cell block it reaches, up to 19
 //     times, and keep all of their matrix work: up to 128 channels, or where
 //     the spectra stay in the caches.  2M samples x 64 -> 400 x 400: 2549 /
-//     1363; x 128: 3174 / 2589; x 256: 3858 / 4960; 20,000 x 1024 -> 400 x 400
-//     of 1.2': 500 / 327, 100,000: 628 / 591, 500,000: 1585 / 1778.  Flagged,
-//     2M x 64: 5790 / 2385; x 256: 7525 / 8442.
-F32Kernel f32_kernel(const hcg_plan_s* p, int64_t C) {
+//     1363 / 2716; x 128: 3174 / 2589 / 2842; x 256: 3858 / 4960 / 3767;
+//     20,000 x 1024 -> 400 x 400 of 1.2': 500 / 327 / 533, 100,000: 628 / 591 /
+//     753, 500,000: 1585 / 1778 / 1926.  Flagged, 2M x 64: 5790 / 2385 / 2514;
+//     x 256: 7525 / 8442 / 5190.
+//   - Blocks read a row 3.6 instead of 7.7 times and multiply at 2.7 times the
+//     FP32 matrix rate (flags cost them a third more products, the others
+//     twice as many), but in k-steps of 32 candidates, which a sparse map
+//     fills badly: dense maps (pairs within R per cell) of many channels.
+//     9.12M x 1024 -> 600 x 600 (5500 pairs per cell): 59700 / 97950 / 51000;
+//     500,000 x 1024 -> 200 x 200 (2300): 4047 / 5094 / 3692; -> 400 x 400
+//     (570): 3734 / 4237 / 4061.  Flagged, 500,000 x 256 -> 400 x 400 (570):
+//     2081 / 2241 / 1744, 2M x 128 (2300): 7109 / 4299 / 3099.
+F32Kernel f32_kernel(const hcg_plan_s* p, int64_t C, bool mask) {
   const bool cached = (double)p->n * (double)C * 4.0 <= 100e6;
+  // pairs within R per cell if the samples cover the map evenly
+  const double cells = (double)p->grid.nx * p->grid.ny;
+  const double area = cells * std::fabs(p->grid.dlon * p->grid.dlat);
+  const double pairs =
+      area > 0.0 ? (double)p->n * kPi * p->support_deg * p->support_deg / area : 0.0;
+  const int64_t slab = mask ? kBlockSlabFlagged : kBlockSlab;
+  const bool block = p->bmaxr && p->kern.type == kGauss && support_chord2(p) < kNarrowChord2 &&
+                     !cached && (mask ? C > 64 && pairs >= 500.0 : C >= 512 && pairs >= 2000.0) &&
+                     (int64_t)p->bntx * p->bnty * ((C + slab - 1) / slab) >= kFewBlocks;
+  if (block) return F32Kernel::kBlock;
   return C <= 128 || cached ? F32Kernel::kWave : F32Kernel::kTile;
 }
 
@@ -97,8 +119,11 @@ static hcg_status launch_mfma(const hcg_plan_s* p, const void* spec, const void*
                               hipStream_t stream, float* wcube = nullptr) {
   static_assert(!(kPacked && kForm == kF32), "plan-ordered spectra are a low-precision input");
   if constexpr (kForm == kF32) {
-    if (f32_kernel(p, C) == F32Kernel::kWave)
+    const F32Kernel k = f32_kernel(p, C, kMask);
+    if (k == F32Kernel::kWave)
       return launch_wave(p, (const float*)spec, C, cube, wmap, wcube, kMask, stream);
+    if (k == F32Kernel::kBlock)
+      return launch_block(p, (const float*)spec, C, cube, wmap, wcube, kMask, stream);
   }
   GatherArgs a = plan_args(p);
   a.wcube = wcube;

@@ -118,11 +118,13 @@ __device__ __forceinline__ uint32_t wave_scan_max(uint32_t x, int lane) {
 // order only decides which of them share a matrix-core step.  A tile's
 // ranges then take up to twice their number of entries, so a tile of more
 // than kMaxRangesLimit / 2 ranges (a ring split at longitude 0 gives two)
-// keeps the plan's order.
+// keeps the plan's order.  *s_count, where given (with widening or rotation),
+// receives the number of staged ranges.
 constexpr uint32_t kPhaseQuantum = 128;
 template <bool kPhase = false>
 __device__ inline uint32_t stage_ranges(const uint2* __restrict__ ranges, uint32_t nr, uint2* s_rng,
-                                        uint32_t* s_pre, uint32_t npad = 0) {
+                                        uint32_t* s_pre, uint32_t npad = 0,
+                                        uint32_t* s_count = nullptr) {
   const int nt = blockDim.x;
   // rotated: the plan's ranges go to the upper half and the staged ones are
   // written from the start; a chunk of 64 reads its entries before it
@@ -193,6 +195,7 @@ __device__ inline uint32_t stage_ranges(const uint2* __restrict__ ranges, uint32
     if (l == 0) {
       s_pre[o] = acc;
       s_pre[kMaxRangesLimit] = acc;
+      if (s_count) *s_count = o;
     }
   }
   __syncthreads();

@@ -24,6 +24,7 @@ constexpr uint64_t kPlanMagic = 0x48434750'4c414e31ull;  // "HCGPLAN1"
 constexpr int kTileX = 8;
 constexpr int kTileY = 8;
 constexpr int kTileCells = kTileX * kTileY;
+constexpr int kBlockCells = 16;  // cells of a gather block per side
 constexpr int kMaxRangesLimit = 1024;
 
 // ---------------------------------------------------------------------------
@@ -200,6 +201,11 @@ struct hcg_plan_s {
   uint2* ranges;       // [ntiles][maxr] candidate ranges [a, b)
   uint32_t* nranges;   // [ntiles]
   uint32_t* ncand;     // [ntiles] candidates per tile
+  // the same for blocks of 16 x 16 cells (gather_block.h); bmaxr = 0: none
+  // (cells given by their centres, or more rings than the range table holds)
+  int32_t bntx, bnty, bmaxr;
+  uint2* branges;
+  uint32_t* bnranges;
   uint32_t* flags;     // [4] device status words
   double4* cells;      // [ny * nx] unit vectors of the cell centres (NaN: no cell)
 };
@@ -273,9 +279,26 @@ constexpr int kBatchCtl = 16;
 
 // Gathers of FP32 spectra of more than 8 channels, by what a map and channel
 // count are faster with (f32_kernel, gather.hip): 8 x 8 tiles shared by a
-// workgroup (gather_tile.h), independent waves (gather_wave.h).
-enum class F32Kernel { kTile, kWave };
-F32Kernel f32_kernel(const hcg_plan_s* p, int64_t C);
+// workgroup (gather_tile.h), independent waves (gather_wave.h), 16 x 16-cell
+// blocks on split operands (gather_block.h).
+enum class F32Kernel { kTile, kWave, kBlock };
+F32Kernel f32_kernel(const hcg_plan_s* p, int64_t C, bool mask);
+
+// 16 x 16-cell blocks (gather_block.hip): linear grids and narrow Gaussians
+// (those with block ranges); mask: flagged values.
+constexpr int64_t kBlockSlab = 256, kBlockSlabFlagged = 128;  // channels of a workgroup
+hcg_status launch_block(const hcg_plan_s* p, const float* spec, int64_t C, float* cube, float* wmap,
+                        float* wcube, bool mask, hipStream_t stream);
+// Rows read two channels at a time.
+bool block_rows2(const void* spec, int64_t C);
+// The plan's block ranges in a gather's arguments, in place of its tiles'; the
+// series factors of the weights travel in the elliptical kernel's fields,
+// which a Gaussian leaves unused.
+void block_args(const hcg_plan_s* p, GatherArgs* a);
+// The unflagged gather of a batch's fields: one workgroup per item, or `blocks`
+// persistent ones.
+void launch_block_items(bool vec, bool items, uint32_t blocks, const GatherArgs* fields,
+                        const BatchSeg* segs, uint32_t nseg, uint32_t* ctl, hipStream_t stream);
 
 // Independent waves (gather_wave.hip): any kernel shape, flagged or not.
 // wave_shape: 16-channel tiles of a wave and waves of a cell block, for a plan

@@ -468,7 +468,7 @@ __device__ void tile_ranges_wave(const uint32_t* __restrict__ keys,
   if (__ballot(overflow) && lane == 0) atomicOr(&flags[0], 1u);
   if (lane == 0) {
     *nranges_out = min(count, (uint32_t)maxr);
-    *ncand_out = total;
+    if (ncand_out) *ncand_out = total;
   }
 }
 
@@ -477,16 +477,17 @@ __device__ void tile_ranges_wave(const uint32_t* __restrict__ keys,
 __device__ inline void tile_ranges_linear(const uint32_t* __restrict__ keys,
                                           const uint32_t* __restrict__ csr, int ns,
                                           int ring_first, int ring_last, uint32_t pix_base,
-                                          const GridGeom& g, int ntx, int nty, double support_rad,
-                                          int maxr, uint2* __restrict__ ranges,
+                                          const GridGeom& g, int ntx, int nty, int tcells,
+                                          double support_rad, int maxr,
+                                          uint2* __restrict__ ranges,
                                           uint32_t* __restrict__ nranges,
                                           uint32_t* __restrict__ ncand,
                                           uint32_t* __restrict__ flags, uint32_t bx) {
   const int tile = (int)bx * 4 + (threadIdx.x >> 6);
   if (tile >= ntx * nty) return;
   const int tx = tile % ntx, ty = tile / ntx;
-  const int ix0 = tx * kTileX, ix1 = min(g.nx, ix0 + kTileX) - 1;
-  const int iy0 = ty * kTileY, iy1 = min(g.ny, iy0 + kTileY) - 1;
+  const int ix0 = tx * tcells, ix1 = min(g.nx, ix0 + tcells) - 1;
+  const int iy0 = ty * tcells, iy1 = min(g.ny, iy0 + tcells) - 1;
   double lon_a = cell_lon_deg(g, ix0) * kDeg2Rad, lon_b = cell_lon_deg(g, ix1) * kDeg2Rad;
   double lat_a = cell_lat_deg(g, iy0) * kDeg2Rad, lat_b = cell_lat_deg(g, iy1) * kDeg2Rad;
   if (lon_a > lon_b) { const double t = lon_a; lon_a = lon_b; lon_b = t; }
@@ -497,16 +498,30 @@ __device__ inline void tile_ranges_linear(const uint32_t* __restrict__ keys,
   // conservative support: absorbs rounding of every bound below
   const double Rs = support_rad * (1.0 + 1e-9) + 1e-12;
   tile_ranges_wave(keys, csr, ns, ring_first, ring_last, pix_base, lon_a, lon_b, lat_a, lat_b, Rs,
-                   maxr, ranges + (int64_t)tile * maxr, &nranges[tile], &ncand[tile], flags);
+                   maxr, ranges + (int64_t)tile * maxr, &nranges[tile],
+                   ncand ? &ncand[tile] : nullptr, flags);
 }
 
+// Tiles of 8 x 8 cells, then (from block (ntx nty + 3) / 4 on) blocks of 16 x
+// 16: one launch for both.
+struct BlockRanges {
+  int ntx, nty, maxr;
+  uint2* ranges;
+  uint32_t* nranges;
+};
 __global__ void __launch_bounds__(256) k_tile_ranges(
     const uint32_t* __restrict__ keys, const uint32_t* __restrict__ csr, int ns, int ring_first,
     int ring_last, uint32_t pix_base, GridGeom g, int ntx, int nty, double support_rad, int maxr,
     uint2* __restrict__ ranges, uint32_t* __restrict__ nranges, uint32_t* __restrict__ ncand,
-    uint32_t* __restrict__ flags) {
-  tile_ranges_linear(keys, csr, ns, ring_first, ring_last, pix_base, g, ntx, nty, support_rad,
-                     maxr, ranges, nranges, ncand, flags, blockIdx.x);
+    uint32_t* __restrict__ flags, BlockRanges br) {
+  const uint32_t nt = (uint32_t)(ntx * nty + 3) / 4;
+  if (blockIdx.x < nt)
+    tile_ranges_linear(keys, csr, ns, ring_first, ring_last, pix_base, g, ntx, nty, kTileX,
+                       support_rad, maxr, ranges, nranges, ncand, flags, blockIdx.x);
+  else
+    tile_ranges_linear(keys, csr, ns, ring_first, ring_last, pix_base, g, br.ntx, br.nty,
+                       kBlockCells, support_rad, br.maxr, br.ranges, br.nranges, nullptr, flags,
+                       blockIdx.x - nt);
 }
 
 // Cells given by their centres: per tile (one wave), the cap around the
@@ -589,7 +604,7 @@ enum FieldBlockKind : int {
   kFbOne = 3,        // one block per field
   kFbCells = 4,      // ceil(cells / 256)
   kFbRings = 5,      // ceil((rings + 1) / 256)
-  kFbTiles = 6,      // ceil(tiles / 4)
+  kFbTiles = 6,      // ceil(tiles / 4) + ceil(16 x 16 blocks / 4)
   kFbKinds = 7
 };
 
@@ -611,6 +626,7 @@ struct PlanField {
   uint32_t *keys, *perm, *csr, *nranges, *ncand, *flags;
   uint2* ranges;
   double4 *xyz, *cells;
+  BlockRanges br;
 };
 
 // The field of flattened block b of launch kind `kind`, and its block there.
@@ -774,8 +790,15 @@ __global__ void __launch_bounds__(256) k_tile_ranges_fields(const PlanField* __r
                                                             const uint32_t* __restrict__ prefix,
                                                             int nf) {
   HCG_FIELD_BLOCK(kFbTiles);
-  tile_ranges_linear(F.keys, F.csr, F.nside, F.ring_first, F.ring_last, F.pix_base, F.grid, F.ntx,
-                     F.nty, F.support_rad, F.maxr, F.ranges, F.nranges, F.ncand, F.flags, lb);
+  const uint32_t nt = (uint32_t)(F.ntx * F.nty + 3) / 4;
+  if (lb < nt)
+    tile_ranges_linear(F.keys, F.csr, F.nside, F.ring_first, F.ring_last, F.pix_base, F.grid, F.ntx,
+                       F.nty, kTileX, F.support_rad, F.maxr, F.ranges, F.nranges, F.ncand, F.flags,
+                       lb);
+  else
+    tile_ranges_linear(F.keys, F.csr, F.nside, F.ring_first, F.ring_last, F.pix_base, F.grid,
+                       F.br.ntx, F.br.nty, kBlockCells, F.support_rad, F.br.maxr, F.br.ranges,
+                       F.br.nranges, nullptr, F.flags, lb - nt);
 }
 #undef HCG_FIELD_BLOCK
 
@@ -794,6 +817,13 @@ static int bit_length(uint32_t v) {
   int b = 0;
   while (v) { ++b; v >>= 1; }
   return b;
+}
+
+// Candidate-range slots of a 16 x 16-cell block (two per ring of its latitude
+// span + 2R), or 0 where the gather's range table has no room for them.
+static int block_max_ranges(double dlat_rad, double R, int nside) {
+  const double rings = ((kBlockCells - 1) * dlat_rad + 2.0 * R) / (2.0 / (3.0 * nside)) + 6.0;
+  return rings > kMaxRangesLimit / 2 ? 0 : 2 * (int)std::ceil(rings);
 }
 
 // Freed memory the pool keeps for reuse (a plan of the 20M-sample cube
@@ -1097,6 +1127,8 @@ struct PlanBuilder {
                   "%s: support or tile too wide for nside %d (%.0f rings per tile; at most %d)", who,
                   nside, rings_d, kMaxRangesLimit / 2);
     const int maxr = 2 * (int)std::ceil(rings_d);
+    const int bntx = (nx + kBlockCells - 1) / kBlockCells, bnty = (ny + kBlockCells - 1) / kBlockCells;
+    const int bmaxr = tg.grid ? block_max_ranges(std::fabs(tg.grid->dlat_deg) * kDeg2Rad, R, nside) : 0;
 
     // plan arena
     size_t off = 0;
@@ -1111,6 +1143,8 @@ struct PlanBuilder {
     const size_t o_rng = take(sizeof(uint2) * (size_t)ntiles * maxr);
     const size_t o_nr = take(sizeof(uint32_t) * ntiles);
     const size_t o_nc = take(sizeof(uint32_t) * ntiles);
+    const size_t o_brng = take(sizeof(uint2) * (size_t)bntx * bnty * bmaxr);
+    const size_t o_bnr = take(sizeof(uint32_t) * (size_t)bntx * bnty);
     const size_t o_flags = take(16);
     const size_t o_cells = take(sizeof(double4) * ncell);
     const size_t arena_bytes = off;
@@ -1157,6 +1191,11 @@ struct PlanBuilder {
     p->ranges = (uint2*)(A + o_rng);
     p->nranges = (uint32_t*)(A + o_nr);
     p->ncand = (uint32_t*)(A + o_nc);
+    p->bntx = bntx;
+    p->bnty = bnty;
+    p->bmaxr = bmaxr;
+    p->branges = (uint2*)(A + o_brng);
+    p->bnranges = (uint32_t*)(A + o_bnr);
     p->flags = (uint32_t*)(A + o_flags);
     p->cells = (double4*)(A + o_cells);
 
@@ -1180,9 +1219,11 @@ struct PlanBuilder {
     HCG_LAUNCH_CHECK("k_ring_csr");
     HCG_HIP(hipMemsetAsync(p->flags, 0, 16, stream));
     if (tg.grid) {
-      k_tile_ranges<<<(unsigned)((ntiles + 3) / 4), 256, 0, stream>>>(
+      const int64_t nblk = bmaxr ? (int64_t)bntx * bnty : 0;
+      k_tile_ranges<<<(unsigned)((ntiles + 3) / 4 + (nblk + 3) / 4), 256, 0, stream>>>(
           p->keys, p->csr, nside, ring_first, ring_last, pix_base, p->grid, ntx, nty, R, maxr,
-          p->ranges, p->nranges, p->ncand, p->flags);
+          p->ranges, p->nranges, p->ncand, p->flags,
+          BlockRanges{bntx, bnty, bmaxr, p->branges, p->bnranges});
       HCG_LAUNCH_CHECK("k_tile_ranges");
     } else {
       k_tile_ranges_cap<<<(unsigned)((ntiles + 3) / 4), 256, 0, stream>>>(
@@ -1367,7 +1408,7 @@ hcg_status plan_build_fields(int32_t nf, const hcg_field_desc* fd, const hcg_opt
   std::vector<uint32_t> pix_max_of(nf);
   size_t arena_bytes = 0, t2 = 0;
   std::vector<size_t> o_t2(nf);
-  struct Off { size_t xyz, keys, perm, csr, rng, nr, nc, flags, cells, bytes; };
+  struct Off { size_t xyz, keys, perm, csr, rng, nr, nc, brng, bnr, flags, cells, bytes; };
   std::vector<Off> off(nf);
   for (int32_t f = 0; f < nf; ++f) {
     PlanField& P = F[f];
@@ -1404,6 +1445,11 @@ hcg_status plan_build_fields(int32_t nf, const hcg_field_desc* fd, const hcg_opt
     a.rng = take(sizeof(uint2) * (size_t)ntiles * P.maxr);
     a.nr = take(sizeof(uint32_t) * ntiles);
     a.nc = take(sizeof(uint32_t) * ntiles);
+    P.br.ntx = (P.grid.nx + kBlockCells - 1) / kBlockCells;
+    P.br.nty = (P.grid.ny + kBlockCells - 1) / kBlockCells;
+    P.br.maxr = block_max_ranges(std::fabs(P.grid.dlat) * kDeg2Rad, P.support_rad, P.nside);
+    a.brng = take(sizeof(uint2) * (size_t)P.br.ntx * P.br.nty * P.br.maxr);
+    a.bnr = take(sizeof(uint32_t) * (size_t)P.br.ntx * P.br.nty);
     a.flags = take(16);
     a.cells = take(sizeof(double4) * ncell);
     a.bytes = at;
@@ -1436,6 +1482,8 @@ hcg_status plan_build_fields(int32_t nf, const hcg_field_desc* fd, const hcg_opt
     P.ranges = (uint2*)(A + a.rng);
     P.nranges = (uint32_t*)(A + a.nr);
     P.ncand = (uint32_t*)(A + a.nc);
+    P.br.ranges = (uint2*)(A + a.brng);
+    P.br.nranges = (uint32_t*)(A + a.bnr);
     P.flags = (uint32_t*)(A + a.flags);
     P.cells = (double4*)(A + a.cells);
     char* t = (char*)temp2.p + o_t2[f];
@@ -1458,7 +1506,10 @@ hcg_status plan_build_fields(int32_t nf, const hcg_field_desc* fd, const hcg_opt
   const uint64_t nb_scan = prefix(kFbScan, [](const PlanField& P) { return (uint64_t)P.rs_np; });
   prefix(kFbOne, [](const PlanField&) { return (uint64_t)1; });
   const uint64_t nb_rings = prefix(kFbRings, [](const PlanField& P) { return (uint64_t)((P.nrings + 1 + 255) / 256); });
-  const uint64_t nb_tiles = prefix(kFbTiles, [](const PlanField& P) { return (uint64_t)(((int64_t)P.ntx * P.nty + 3) / 4); });
+  const uint64_t nb_tiles = prefix(kFbTiles, [](const PlanField& P) {
+    return (uint64_t)(((int64_t)P.ntx * P.nty + 3) / 4) +
+           (P.br.maxr ? (uint64_t)(((int64_t)P.br.ntx * P.br.nty + 3) / 4) : 0);
+  });
   if (nb_cells + nb_samples >= 0xFFFFFFF0ull || nb_tiles >= 0xFFFFFFF0ull)
     return fail(HCG_E_UNSUPPORTED, "hcg_plan_batch: too many cells");
   memcpy(h_tab, F.data(), sizeof(PlanField) * nf);
@@ -1527,6 +1578,11 @@ hcg_status plan_build_fields(int32_t nf, const hcg_field_desc* fd, const hcg_opt
     p->ranges = P.ranges;
     p->nranges = P.nranges;
     p->ncand = P.ncand;
+    p->bntx = P.br.ntx;
+    p->bnty = P.br.nty;
+    p->bmaxr = P.br.maxr;
+    p->branges = P.br.ranges;
+    p->bnranges = P.br.nranges;
     p->flags = P.flags;
     p->cells = P.cells;
     p->arena = nullptr;  // in the shared arena

@@ -1,7 +1,8 @@
-"""The independent waves that FP32 maps of more than 8 channels take besides
-the 8 x 8-cell tiles, at the edges of their ranges: channel groups of 64, 128
-and 256 cut short, rows read four channels or one at a time, one or four waves
-to a cell block, flags.
+"""The two gathers that FP32 maps of more than 8 channels take besides the
+8 x 8-cell tiles, at the edges of their ranges: independent waves (channel
+groups of 64, 128 and 256 cut short, rows read four channels or one at a
+time, one or four waves to a cell block, flags) and 16 x 16-cell blocks
+(ragged blocks and slabs, flags, values that BF16 pieces cannot hold).
 Bounds against the FP64 oracle are the FP32 form's: 1e-5 per channel, W to
 1e-6 (1e-5 for the flagged form's FP32 weight sums); the few-channel gather
 (FP64 sums) is held to the same bound where it stands in for the oracle."""
@@ -12,7 +13,8 @@ import torch
 import oracle
 import paper_2012_13173_amd as hcg
 import synth
-from tests.gridcheck import (assert_cube_close, assert_weights_close, sample_cells)
+from tests.gridcheck import (assert_cube_close, assert_weights_close, gather_cells, sample_cells,
+                             sampled_oracle)
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
@@ -83,7 +85,8 @@ def test_independent_waves_match_the_oracle(n, nchan, nx, ny, cell, fwhm, shift,
 
 @pytest.mark.parametrize("n,nchan", [(20_000, 12), (2_000_000, 129)])
 def test_flagged_form_without_channel_weights(n, nchan):
-    """No array for the channels' weights; spectra on either side of the caches."""
+    """The waves' and the blocks' flagged kernels and a spectra size on either
+    side of the caches; no array for the channels' weights."""
     w = synth.small_cube(n=n // 10, nchan=1, nx=260, ny=250, cell_arcmin=0.5, seed=2700)
     g = torch.Generator().manual_seed(2701)
     lon = w.lon.repeat(10) + torch.randn(n, generator=g, dtype=torch.float64) * 1e-3
@@ -107,3 +110,73 @@ def test_flagged_form_without_channel_weights(n, nchan):
         assert_cube_close(cube[c:c + 1].cpu().numpy(), one.cpu().numpy(), 1e-5, f"channel {c}")
         assert_weights_close(W[c].cpu().numpy(), W1[0].cpu().numpy(), rtol=1e-5)
     plan.destroy()
+
+
+# dense maps whose spectra outgrow the caches: ragged blocks, a slab cut short
+# (one channel, an odd count, rows that are not 8-byte aligned)
+BLOCK = [(60_000, 513, 261, 253, 0.14, 0), (60_000, 514, 257, 256, 0.14, 0),
+         (60_000, 512, 250, 271, 0.14, 1)]
+
+
+@pytest.mark.parametrize("n,nchan,nx,ny,cell,shift", BLOCK)
+def test_blocks_match_the_oracle(n, nchan, nx, ny, cell, shift):
+    w = synth.small_cube(n=n, nchan=nchan, nx=nx, ny=ny, cell_arcmin=cell, seed=2800 + nchan)
+    plan = hcg.hcg_plan(w.lon.to(DEV), w.lat.to(DEV), w.grid, w.fwhm_deg, w.support_deg)
+    rows = _device_rows(w.spectra, shift)
+    cube = torch.full((nchan, ny, nx), 12345.0, device=DEV)
+    W = torch.full((ny, nx), -1.0, device=DEV)
+    print(f"blocks n={n} C={nchan} {nx}x{ny}", flush=True)
+    hcg.hcg_grid(plan, rows, cube, W)
+    torch.cuda.synchronize()
+    groups = sample_cells(w.grid, seed=6, patches=4, patch=5)
+    ref = [sampled_oracle(w, c) for c in groups]
+    V, Wg = gather_cells(cube, W, np.concatenate(groups))
+    assert_cube_close(V.T, np.concatenate([v for v, _ in ref]).T, 1e-5, f"C={nchan}")
+    assert_weights_close(Wg, np.concatenate([x for _, x in ref]))
+
+    # values that are not finite, or that rounding to BF16 would overflow:
+    # the cells within R of them, and those alone (the few-channel gather's rule)
+    chans = [0, 1, 2, 3, nchan - 1]
+    top = torch.finfo(torch.float32).max
+    plants = [(0, 0, float("inf")), (0, n // 3, float("-inf")), (1, n // 2, float("nan")),
+              (2, n // 4, top), (2, n // 5, -top), (3, 7, 1e-40), (3, 8, -float("inf")),
+              (nchan - 1, n - 1, float("inf")), (nchan - 1, n - 2, float("nan"))]
+    for c, s, v in plants:
+        rows[s, c] = v
+    hcg.hcg_grid(plan, rows, cube, W)
+    few = torch.empty((len(chans), ny, nx), device=DEV)
+    hcg.hcg_grid(plan, rows[:, chans].contiguous(), few, W)
+    torch.cuda.synchronize()
+    for k, c in enumerate(chans):
+        got, want = cube[c].cpu().numpy(), few[k].cpu().numpy()
+        assert np.array_equal(np.isnan(got), np.isnan(want)), c
+        inf = np.isinf(want)
+        assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], want[inf]), c
+        ok = np.isfinite(want)
+        scale = np.abs(want[ok].astype(np.float64)).max()
+        assert np.abs(got[ok].astype(np.float64) - want[ok]).max() <= 1e-5 * scale, c
+    others = [c for c in range(nchan) if c not in chans]
+    assert bool(torch.isfinite(cube[others]).all())
+    plan.destroy()
+
+
+@pytest.mark.parametrize("launch", ["persistent", "items"])
+def test_a_block_field_of_a_batch_equals_its_single_call(launch):
+    ws = [synth.small_cube(n=n, nchan=c, nx=nx, ny=ny, cell_arcmin=0.14, seed=2900 + c)
+          for n, c, nx, ny in ((60_000, 514, 261, 253), (5000, 70, 40, 33), (60_000, 513, 250, 264))]
+    plan_of = lambda w: (w.lon.to(DEV), w.lat.to(DEV), w.grid, w.fwhm_deg, w.support_deg)  # noqa: E731
+    batch = hcg.hcg_plan_batch([plan_of(w) for w in ws], launch=launch)
+    spectra = [w.spectra.to(DEV).contiguous() for w in ws]
+    cubes = [torch.full((w.nchan, w.grid.ny, w.grid.nx), -7.0, device=DEV) for w in ws]
+    wts = [torch.full((w.grid.ny, w.grid.nx), -7.0, device=DEV) for w in ws]
+    print(f"batch of blocks {launch}", flush=True)
+    hcg.hcg_grid_batch(batch, spectra, cubes, wts)
+    torch.cuda.synchronize()
+    for w, s, cube, W in zip(ws, spectra, cubes, wts):
+        plan = hcg.hcg_plan(*plan_of(w))
+        one, W1 = torch.empty_like(cube), torch.empty_like(W)
+        hcg.hcg_grid(plan, s, one, W1)
+        torch.cuda.synchronize()
+        assert torch.equal(one.view(torch.int32), cube.view(torch.int32))
+        assert torch.equal(W1.view(torch.int32), W.view(torch.int32))
+        plan.destroy()
