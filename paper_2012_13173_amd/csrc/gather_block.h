@@ -569,7 +569,6 @@ __device__ __forceinline__ void gather_block(const GatherArgs& a, int tile, int 
     __syncthreads();
 
     const float qnan = __builtin_nanf("");
-    const bool st4 = (g.nx % 4 == 0) && (((uintptr_t)a.cube & 15u) == 0);
 #pragma unroll
     for (int cb = 0; cb < kCB; ++cb) {
       const int y = y0 + (cb / kT) * 4 + lg;
@@ -584,7 +583,7 @@ __device__ __forceinline__ void gather_block(const GatherArgs& a, int tile, int 
         inv[r] = has[r] ? (float)(1.0 / wt) : 0.f;
       }
       const int64_t at = (int64_t)y * g.nx + x;
-      const bool full = st4 && x + 3 < g.nx;
+      const bool full = x + 3 < g.nx;
 #pragma unroll
       for (int j = 0; j < kJ; ++j) {
         const int64_t ch = ch0 + j;
@@ -612,9 +611,9 @@ __device__ __forceinline__ void gather_block(const GatherArgs& a, int tile, int 
           }
         }
         float* wdst = kMask && a.wcube ? a.wcube + ch * G + at : nullptr;
-        if (full && (!kMask || ((uintptr_t)wdst & 15u) == 0)) {
-          *(floatx4*)dst = floatx4{v[0], v[1], v[2], v[3]};
-          if (kMask && wdst) *(floatx4*)wdst = floatx4{wc[0], wc[1], wc[2], wc[3]};
+        if (full) {
+          store4(dst, v);
+          if (kMask && wdst) store4(wdst, wc);
         } else {
 #pragma unroll
           for (int r = 0; r < 4; ++r)

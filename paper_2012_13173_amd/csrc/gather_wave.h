@@ -338,8 +338,7 @@ __device__ __forceinline__ void gather_wave(const GatherArgs& a, int tile, int s
   if (y >= g.ny || x0 >= g.nx) return;
   const float qnan = __builtin_nanf("");
   const int64_t at = (int64_t)y * g.nx + x0;
-  const bool full = g.nx % 4 == 0 && (((uintptr_t)a.cube & 15u) == 0) &&
-                    (!kMask || ((uintptr_t)a.wcube & 15u) == 0);
+  const bool full = x0 + 3 < g.nx;
 #pragma unroll
   for (int j = 0; j < kJ; ++j) {
     const int64_t ch = c_w + (kVec ? 64 * (j >> 2) + 4 * li + (j & 3) : 16 * j + li);
@@ -357,8 +356,8 @@ __device__ __forceinline__ void gather_wave(const GatherArgs& a, int tile, int s
     float* dst = a.cube + ch * G + at;
     float* wdst = kMask && a.wcube ? a.wcube + ch * G + at : nullptr;
     if (full) {
-      *(floatx4*)dst = floatx4{v[0], v[1], v[2], v[3]};
-      if (kMask && wdst) *(floatx4*)wdst = floatx4{wc[0], wc[1], wc[2], wc[3]};
+      store4(dst, v);
+      if (kMask && wdst) store4(wdst, wc);
     } else {
 #pragma unroll
       for (int r = 0; r < 4; ++r)
