@@ -46,7 +46,11 @@ constexpr int kClsWave = 13;
 // FP32 by blocks of 16 x 16 cells (gather_block.hip), rows read two channels
 // or one at a time.
 constexpr int kClsBlock = 17;
-constexpr int kClasses = 19;
+// FP32, C = 1 or C <= 8, fields whose tiles have few candidates: one wave to a
+// tile; and the sub-blocks of C <= 8.
+constexpr int kClsLane = 19, kClsLane8 = 20, kClsCells8 = 21;
+constexpr int kClasses = 22;
+constexpr bool few_cls(int cls) { return cls == kClsCells || cls >= kClsLane; }
 constexpr int wave_cls(int j, bool vec) { return kClsWave + (j == 8 ? 1 : 0) + (vec ? 0 : 2); }
 constexpr int wave_cls_j(int cls) { return (cls - kClsWave) & 1 ? 8 : 4; }
 
@@ -64,35 +68,25 @@ constexpr int kCellsWaves = 4;
 
 // Sub-blocks 4 part .. 4 part + 3 of a tile (C = 1 has part 0 only, C <= 8
 // parts 0 .. 3).
-constexpr int kCellsParts = CellsShape<8, false>::kSubs / kCellsWaves;
-template <bool kWide>
-__device__ inline void cells_item(const GatherArgs& a, int tile, int part, unsigned char* lds) {
-  if (a.C == 1) cells_tile<1, false, kWide, false>(a, tile, 0, kCellsWaves, 1, lds);
-  else cells_tile<8, false, kWide, false>(a, tile, part * kCellsWaves, kCellsWaves, 1, lds);
-}
-static_assert(CellsShape<1, false>::kSubs == kCellsWaves, "one sub-block per wave at C = 1");
-constexpr size_t cells_batch_lds_bytes(int maxr) {
-  const size_t one = cells_lds_size<16, 2, false>(kCellsWaves, kCellsWaves, maxr);
-  const size_t many = cells_lds_size<4, 9, false>(kCellsWaves, kCellsWaves, maxr);
-  return one > many ? one : many;
-}
+template <int kCM>
+constexpr int kCellsParts = CellsShape<kCM, false>::kSubs / kCellsWaves;
 
 // One workgroup per item and part (blockIdx.y):
-template <bool kWide>
-__global__ void __launch_bounds__(256, 3) k_cells_items(const GatherArgs* __restrict__ fields,
+template <int kCM, bool kWide>
+__global__ void __launch_bounds__(256) k_cells_items(const GatherArgs* __restrict__ fields,
                                                      const BatchSeg* __restrict__ segs,
                                                      uint32_t nseg) {
   extern __shared__ __align__(32) unsigned char s_dyn[];
   const uint32_t it = blockIdx.x;
   const BatchSeg sg = batch_seg_of(segs, nseg, it);
-  const GatherArgs& a = fields[sg.field];
-  if (blockIdx.y > 0 && a.C == 1) return;
-  cells_item<kWide>(a, (int)(it - sg.base), (int)blockIdx.y, s_dyn);
+  const GatherArgs a = fields[sg.field];
+  cells_tile<kCM, false, kWide, false>(a, (int)(it - sg.base), (int)blockIdx.y * kCellsWaves,
+                                       kCellsWaves, 1, s_dyn);
 }
 
 // Persistent workgroups (four per CU) popping items:
-template <bool kWide>
-__global__ void __launch_bounds__(256, 3) k_cells_batch(const GatherArgs* __restrict__ fields,
+template <int kCM, bool kWide>
+__global__ void __launch_bounds__(256) k_cells_batch(const GatherArgs* __restrict__ fields,
                                                      const BatchSeg* __restrict__ segs,
                                                      uint32_t* __restrict__ ctl) {
   extern __shared__ __align__(32) unsigned char s_dyn[];
@@ -105,13 +99,44 @@ __global__ void __launch_bounds__(256, 3) k_cells_batch(const GatherArgs* __rest
     const uint32_t it = batch_next_item(ctl, total, home, &k, &s_item);
     if (it == 0xFFFFFFFFu) break;
     const BatchSeg sg = batch_seg_of(segs, nseg, it);
-    const GatherArgs& a = fields[sg.field];
-    const int parts = a.C == 1 ? 1 : kCellsParts;
+    const GatherArgs a = fields[sg.field];
 #pragma nounroll
-    for (int part = 0; part < parts; ++part) {
-      cells_item<kWide>(a, (int)(it - sg.base), part, s_dyn);
+    for (int part = 0; part < kCellsParts<kCM>; ++part) {
+      cells_tile<kCM, false, kWide, false>(a, (int)(it - sg.base), part * kCellsWaves, kCellsWaves,
+                                           1, s_dyn);
       __syncthreads();
     }
+  }
+}
+
+// The same for tiles of few candidates: workgroups of one wave.
+template <int kCM, bool kWide>
+__global__ void __launch_bounds__(64) k_lane_items(const GatherArgs* __restrict__ fields,
+                                                   const BatchSeg* __restrict__ segs,
+                                                   uint32_t nseg) {
+  extern __shared__ __align__(32) unsigned char s_dyn[];
+  const uint32_t it = blockIdx.x;
+  const BatchSeg sg = batch_seg_of(segs, nseg, it);
+  const GatherArgs a = fields[sg.field];
+  cells_lane<kCM, false, kWide, false>(a, (int)(it - sg.base), s_dyn);
+}
+
+template <int kCM, bool kWide>
+__global__ void __launch_bounds__(64) k_lane_batch(const GatherArgs* __restrict__ fields,
+                                                   const BatchSeg* __restrict__ segs,
+                                                   uint32_t* __restrict__ ctl) {
+  extern __shared__ __align__(32) unsigned char s_dyn[];
+  __shared__ uint32_t s_item;
+  const uint32_t total = ctl[8], nseg = ctl[9];
+  const int home = (int)(blockIdx.x % kBatchXcds);
+  int k = 0;
+  for (;;) {
+    const uint32_t it = batch_next_item(ctl, total, home, &k, &s_item);
+    if (it == 0xFFFFFFFFu) break;
+    const BatchSeg sg = batch_seg_of(segs, nseg, it);
+    const GatherArgs a = fields[sg.field];
+    cells_lane<kCM, false, kWide, false>(a, (int)(it - sg.base), s_dyn);
+    __syncthreads();
   }
 }
 
@@ -217,6 +242,33 @@ void launch_cls(int qw, bool wide, const GatherArgs* fields, const BatchSeg* seg
   else launch_one<kCls, 1, false>(l, fields, segs, ctl, stream);
 }
 
+// Few channels: sub-blocks of four waves, or one wave to a tile (lane).
+template <int kCM, bool kWide>
+void launch_few_w(bool lane, const GatherArgs* fields, const BatchSeg* segs, uint32_t* ctl,
+                  const ClassLaunch& l, hipStream_t stream) {
+  const bool items = l.strategy == kLaunchItems;
+  if (lane) {
+    const size_t lds = cells_lane_lds_size<kCM>(l.cells_maxr);
+    if (items) k_lane_items<kCM, kWide><<<l.nitems, 64, lds, stream>>>(fields, segs, l.nseg);
+    else k_lane_batch<kCM, kWide><<<l.nblocks * 8, 64, lds, stream>>>(fields, segs, ctl);
+    return;
+  }
+  using Sh = CellsShape<kCM, false>;
+  const size_t lds =
+      cells_lds_size<Sh::kNC, Sh::kS, false>(kCellsWaves, kCellsWaves, l.cells_maxr);
+  if (items)
+    k_cells_items<kCM, kWide><<<dim3(l.nitems, kCellsParts<kCM>), 256, lds, stream>>>(fields, segs, l.nseg);
+  else
+    k_cells_batch<kCM, kWide><<<l.nblocks * 2, 256, lds, stream>>>(fields, segs, ctl);
+}
+
+template <int kCM>
+void launch_few(bool lane, bool wide, const GatherArgs* fields, const BatchSeg* segs, uint32_t* ctl,
+                const ClassLaunch& l, hipStream_t stream) {
+  if (wide) launch_few_w<kCM, true>(lane, fields, segs, ctl, l, stream);
+  else launch_few_w<kCM, false>(lane, fields, segs, ctl, l, stream);
+}
+
 hcg_status launch_class(int cls, int qw, bool wide, const GatherArgs* fields,
                         const BatchSeg* segs, uint32_t* ctl, const ClassLaunch& l,
                         hipStream_t stream) {
@@ -225,17 +277,10 @@ hcg_status launch_class(int cls, int qw, bool wide, const GatherArgs* fields,
     HCG_LAUNCH_CHECK("k_batch_reset");
   }
   switch (cls) {
-    case kClsCells: {
-      const size_t lds = cells_batch_lds_bytes(l.cells_maxr);
-      if (l.strategy == kLaunchItems) {
-        if (wide) k_cells_items<true><<<dim3(l.nitems, kCellsParts), 256, lds, stream>>>(fields, segs, l.nseg);
-        else k_cells_items<false><<<dim3(l.nitems, kCellsParts), 256, lds, stream>>>(fields, segs, l.nseg);
-      } else {
-        if (wide) k_cells_batch<true><<<l.nblocks * 2, 256, lds, stream>>>(fields, segs, ctl);
-        else k_cells_batch<false><<<l.nblocks * 2, 256, lds, stream>>>(fields, segs, ctl);
-      }
-      break;
-    }
+    case kClsCells: launch_few<1>(false, wide, fields, segs, ctl, l, stream); break;
+    case kClsLane: launch_few<1>(true, wide, fields, segs, ctl, l, stream); break;
+    case kClsCells8: launch_few<8>(false, wide, fields, segs, ctl, l, stream); break;
+    case kClsLane8: launch_few<8>(true, wide, fields, segs, ctl, l, stream); break;
     case kClsWave: case kClsWave + 1: case kClsWave + 2: case kClsWave + 3:
       launch_wave_items(wave_cls_j(cls), cls < kClsWave + 2, wide, l.strategy == kLaunchItems,
                         l.strategy == kLaunchItems ? l.nitems : (uint32_t)l.nblocks * 2u, fields,
@@ -265,7 +310,10 @@ hcg_status launch_class(int cls, int qw, bool wide, const GatherArgs* fields,
 
 // Kernel class of a field's data (vec: rows read four elements at a time).
 int field_class(const hcg_plan_s* p, const hcg_field_data& d, bool vec) {
-  if (d.dtype == HCG_F32 && d.nchan <= 8) return kClsCells;
+  if (d.dtype == HCG_F32 && d.nchan <= 8)
+    return cells_by_lane(p->load, (int64_t)p->ntx * p->nty, d.nchan == 1 ? 1 : 8)
+               ? (d.nchan == 1 ? kClsLane : kClsLane8)
+               : (d.nchan == 1 ? kClsCells : kClsCells8);
   if (d.dtype == HCG_F32) {
     const F32Kernel k = f32_kernel(p, d.nchan, false);
     if (k == F32Kernel::kWave) return wave_cls(d.nchan <= 64 ? 4 : 8, vec);
@@ -405,7 +453,7 @@ hcg_status build_items(hcg_batch_s* b, const hcg_field_data* data, int qw, int c
   for (size_t f = 0; f < nf; ++f) {
     const int64_t C = data[f].nchan;
     const int cls = b->built_cls[f];
-    const bool cells = cls == kClsCells;
+    const bool cells = few_cls(cls);
     const int64_t width = cells ? C : cls >= kClsBlock ? kBlockSlab
                                   : cls >= kClsWave ? 16 * wave_cls_j(cls) : 256 * b->cls_qw[cls];
     const int64_t slabs = cells ? 1 : (C + width - 1) / width;
@@ -434,13 +482,13 @@ hcg_status build_items(hcg_batch_s* b, const hcg_field_data* data, int qw, int c
       BatchSeg sg = seg[f];
       sg.base = (uint32_t)base;
       host[(size_t)c * nf + nseg++] = sg;
-      const uint64_t span = (strategy == kLaunchItems && c != kClsCells)
+      const uint64_t span = (strategy == kLaunchItems && !few_cls(c))
                                 ? (uint64_t)b->h_fields[f].tiles_per_xcd * 8u
                                 : (uint64_t)sg.ntiles;
       base += span * sg.slabs;
       if (base >= 0x7FFFFFF0ull) return fail(HCG_E_UNSUPPORTED, "hcg_grid_batch: too many items");
       const GatherArgs& a = b->h_fields[f];
-      wide = wide || !(c == kClsCells ? cells_narrow(a.c2R, a.kern) : a.c2R < kNarrowChord2);
+      wide = wide || !(few_cls(c) ? cells_narrow(a.c2R, a.kern) : a.c2R < kNarrowChord2);
     }
     b->nitems[c] = (uint32_t)base;
     b->nseg[c] = nseg;
@@ -620,9 +668,9 @@ extern "C" hcg_status hcg_grid_batch(hcg_batch_t batch, const hcg_field_data* da
     fresh[f] = make_field_args(b->plans[f], d);
     vecs[f] = fresh[f].vec;
     clss[f] = field_class(b->plans[f], d, vecs[f] != 0);
-    if (clss[f] >= kClsBlock) {
+    if (clss[f] == kClsBlock || clss[f] == kClsBlock + 1) {
       block_args(b->plans[f], &fresh[f]);
-    } else if (clss[f] >= kClsWave) {
+    } else if (clss[f] >= kClsWave && clss[f] < kClsBlock) {
       // the same waves to a cell block as hcg_grid takes (the same sums); with
       // several, an item is a cell block
       GatherArgs& a = fresh[f];

@@ -27,20 +27,34 @@ __global__ void __launch_bounds__((kCellsThreads<kCM, kWide>)) k_gather_cells(co
   cells_tile<kCM, kMask, kWide, kGen>(a, tile, (w - tile * per_tile) * subs, subs, nk, s_dyn);
 }
 
-// Waves per sub-block, by the number of sub-blocks: one from two waves per
-// SIMD on, else four, and below a quarter of that as many as a workgroup
-// takes (kMost), which also shortens the last round of workgroups (576
-// sub-blocks of 10^7 samples on 90 x 90 cells: 629 us with eight waves each,
-// 567 us with sixteen).
-constexpr int64_t kCellsFewWaves = 8192;
-
 template <int kCM, bool kMask, bool kWide, bool kGen>
-static void launch_cells_kernel(const GatherArgs& a, hipStream_t stream) {
+__global__ void __launch_bounds__(64) k_gather_lane(const GatherArgs a) {
+  extern __shared__ __align__(32) unsigned char s_dyn[];
+  const int tile = (int)(blockIdx.x & 7) * a.tiles_per_xcd + (int)(blockIdx.x >> 3);
+  if (tile < a.ntiles) cells_lane<kCM, kMask, kWide, kGen>(a, tile, s_dyn);
+}
+
+// Waves per sub-block: no more than fill the chip (four per SIMD; at C = 1,
+// whose sub-blocks of sixteen cells do the most work per candidate, four
+// rounds of them) and two chunks of 64 candidates for each.  Waves 1 / 2 / 4 /
+// 8 / 16, us: 1456 sub-blocks of 393 candidates, C = 2: 15 / 12 / 16 / 22 / 38;
+// 5168 of 651, C = 8: 42 / 48 / 64 / 135; 1352 of 64,000, C = 4: 711 / 429 / 426
+// / 593; 400 of 866, C = 8: 18 / 13 / 11 / 17; C = 1, 5776 of 7100: 353 / 315 /
+// 312 / 344 / 448, 576 of 79,000: eight 629, sixteen 567.
+template <int kCM, bool kMask, bool kWide, bool kGen>
+static void launch_cells_kernel(const GatherArgs& a, const TileLoad& load, hipStream_t stream) {
+  if (cells_by_lane(load, a.ntiles, kCM)) {
+    k_gather_lane<kCM, kMask, kWide, kGen>
+        <<<(unsigned)a.tiles_per_xcd * 8u, 64, cells_lane_lds_size<kCM>(a.maxr), stream>>>(a);
+    return;
+  }
   using Sh = CellsShape<kCM, kMask>;
   const int64_t all = (int64_t)a.ntiles * Sh::kSubs;
   constexpr int kMost = kCellsThreads<kCM, kWide> / 64;
-  const int nk = all >= kCellsFewWaves ? 1 : all >= kCellsFewWaves / 4 ? 4 : kMost;
-  const int subs = nk == 1 ? 4 : 1;
+  constexpr int64_t kWaves = kCM == 1 ? 16384 : 4096;
+  int nk = 1;
+  while (nk < kMost && all * nk * 2 <= kWaves && load.most >= 64.0 * 2 * (nk * 2)) nk *= 2;
+  const int subs = nk >= 4 ? 1 : 4 / nk;
   const int64_t work = all / subs;
   const size_t lds = cells_lds_size<Sh::kNC, Sh::kS, kGen>(subs * nk, subs, a.maxr);
   k_gather_cells<kCM, kMask, kWide, kGen>
@@ -48,11 +62,11 @@ static void launch_cells_kernel(const GatherArgs& a, hipStream_t stream) {
 }
 
 template <bool kMask, bool kWide, bool kGen>
-static void launch_cells_by_c(const GatherArgs& a, hipStream_t stream) {
-  if (a.C == 1) launch_cells_kernel<1, kMask, kWide, kGen>(a, stream);
-  else if (a.C == 2) launch_cells_kernel<2, kMask, kWide, kGen>(a, stream);
-  else if (a.C <= 4) launch_cells_kernel<4, kMask, kWide, kGen>(a, stream);
-  else launch_cells_kernel<8, kMask, kWide, kGen>(a, stream);
+static void launch_cells_by_c(const GatherArgs& a, const TileLoad& load, hipStream_t stream) {
+  if (a.C == 1) launch_cells_kernel<1, kMask, kWide, kGen>(a, load, stream);
+  else if (a.C == 2) launch_cells_kernel<2, kMask, kWide, kGen>(a, load, stream);
+  else if (a.C <= 4) launch_cells_kernel<4, kMask, kWide, kGen>(a, load, stream);
+  else launch_cells_kernel<8, kMask, kWide, kGen>(a, load, stream);
 }
 
 // Values in the plan's order: out[p][c] = spec[perm[p]][c].
@@ -102,13 +116,13 @@ hcg_status launch_cells(const hcg_plan_s* p, const float* spec, int C, float* cu
   // so the common case carries no general weight path in its registers
   const bool gen = p->kern.type != kGauss, narrow = cells_narrow(a.c2R, p->kern);
   if (mask) {
-    if (gen) launch_cells_by_c<true, true, true>(a, stream);
-    else if (narrow) launch_cells_by_c<true, false, false>(a, stream);
-    else launch_cells_by_c<true, true, false>(a, stream);
+    if (gen) launch_cells_by_c<true, true, true>(a, p->load, stream);
+    else if (narrow) launch_cells_by_c<true, false, false>(a, p->load, stream);
+    else launch_cells_by_c<true, true, false>(a, p->load, stream);
   } else {
-    if (gen) launch_cells_by_c<false, true, true>(a, stream);
-    else if (narrow) launch_cells_by_c<false, false, false>(a, stream);
-    else launch_cells_by_c<false, true, false>(a, stream);
+    if (gen) launch_cells_by_c<false, true, true>(a, p->load, stream);
+    else if (narrow) launch_cells_by_c<false, false, false>(a, p->load, stream);
+    else launch_cells_by_c<false, true, false>(a, p->load, stream);
   }
   const hipError_t le = hipGetLastError();
   if (sorted) (void)hipFreeAsync(sorted, stream);

@@ -28,6 +28,8 @@
 // 1.98M samples on 400 x 400 cells of 0.5' (C = 4): 2118 -> 871 us.
 #pragma once
 
+#include <algorithm>
+
 #include "hcg_internal.h"
 #include "sphere.h"
 
@@ -352,6 +354,103 @@ __device__ inline void cells_tile(const GatherArgs& a, int tile, int sub0, int s
       if (kMask && a.wcube) a.wcube[c * G + cell] = (float)wc;
     }
   }
+}
+
+// A whole tile by one wave, one lane per cell: for tiles of few candidates,
+// where the sums across lanes, the sub-blocks' frames and the walks of
+// sixteen sub-blocks (cells_tile) cost more than the candidates do.  Every
+// candidate is read once, by one lane, and handed to the others through LDS.
+template <int kCM>
+__host__ __device__ constexpr size_t cells_lane_lds_size(int maxr) {
+  return (sizeof(double4) + sizeof(float) * kCM) * 64 + sizeof(uint2) * (size_t)maxr +
+         sizeof(uint32_t) * ((size_t)maxr + 1);
+}
+
+template <int kCM, bool kMask, bool kWide, bool kGen>
+__device__ inline void cells_lane(const GatherArgs& a, int tile, unsigned char* base) {
+  constexpr int kW = CellsShape<kCM, kMask>::kW;
+  double4* s_v = (double4*)base;
+  float* s_s = (float*)(s_v + 64);
+  uint2* s_rng = (uint2*)(s_s + 64 * kCM);
+  uint32_t* s_pre = (uint32_t*)(s_rng + a.maxr);
+  const int lane = threadIdx.x;
+  const GridGeom& g = a.g;
+  const int C = (int)a.C;
+  const int ix = (tile % a.ntx) * kTileX + (lane & 7), iy = (tile / a.ntx) * kTileY + (lane >> 3);
+  const CellVec u = cell_at(a.cells, g, ix, iy);  // NaN (no cell): within R of nothing
+  CellFrame f{0.0, 0.0, 0.0, 0.0, 0.0};
+  if constexpr (kGen) {
+    if (a.kern.type == kElliptic) f = cell_frame(u);
+  }
+  const uint32_t nr = a.nranges[tile];
+  const uint32_t total =
+      cells_stage_ranges(a.ranges + (int64_t)tile * a.maxr, nr, s_rng, s_pre);
+  const double w0 = a.kern.wscale, w1 = w0 * (1.0 / 12.0), w2 = w0 * (1.0 / 90.0);
+  double acc[kCM], wsum[kW];
+#pragma unroll
+  for (int c = 0; c < kCM; ++c) acc[c] = 0.0;
+#pragma unroll
+  for (int c = 0; c < kW; ++c) wsum[c] = 0.0;
+
+  uint32_t cur = 0;
+  for (uint32_t q0 = 0; q0 < total; q0 += 64) {
+    const uint32_t pos = cells_cand_pos(min(q0 + lane, total - 1u), s_rng, s_pre, nr, &cur);
+    const double4 v = a.xyz[pos];
+    const float* row = (const float*)a.spec + (int64_t)(a.perm ? a.perm[pos] : pos) * C;
+    float s[kCM];
+#pragma unroll
+    for (int c = 0; c < kCM; ++c) s[c] = row[(kCM == 1 || c < C) ? c : 0];
+    __syncthreads();  // the last chunk has been used
+    s_v[lane] = v;
+#pragma unroll
+    for (int c = 0; c < kCM; ++c) s_s[lane * kCM + c] = s[c];
+    __syncthreads();
+    const int m = (int)min(64u, total - q0);
+#pragma unroll 4
+    for (int k = 0; k < m; ++k) {
+      const double dx = s_v[k].x - u.x, dy = s_v[k].y - u.y, dz = s_v[k].z - u.z;
+      const double c2 = fma(dx, dx, fma(dy, dy, dz * dz));
+      if (c2 <= a.c2R) {
+        double w;
+        if constexpr (kGen) w = pair_weight_gen(a.kern, c2, dx, dy, dz, f);
+        else if constexpr (kWide) w = pair_weight64(c2, a.kern.wscale);
+        else w = (double)__builtin_amdgcn_exp2f((float)(c2 * fma(c2, fma(c2, w2, w1), w0)));
+#pragma unroll
+        for (int c = 0; c < kCM; ++c) {
+          const float x = s_s[k * kCM + c];
+          if (kMask && (__float_as_uint(x) & 0x7F800000u) == 0x7F800000u) continue;
+          acc[c] += w * (double)x;
+          if (kMask) wsum[kMask ? c : 0] += w;
+        }
+        if (!kMask) wsum[0] += w;
+      }
+    }
+  }
+  if (ix >= g.nx || iy >= g.ny) return;
+  const int64_t G = (int64_t)g.nx * g.ny, cell = (int64_t)iy * g.nx + ix;
+  if (!kMask && a.wmap) a.wmap[cell] = (float)wsum[0];
+#pragma unroll
+  for (int c = 0; c < kCM; ++c) {
+    if (c >= C) continue;
+    const double wc = wsum[kMask ? c : 0];
+    a.cube[c * G + cell] = (wc != 0.0) ? (float)(acc[c] / wc) : __builtin_nanf("");
+    if (kMask && a.wcube) a.wcube[c * G + cell] = (float)wc;
+  }
+}
+
+// Whether a plan's tiles are taken by one wave each (cells_lane), kCM channels.
+// In us, fitted to 23 maps of 25 to 5544 tiles of 2 to 64,000 candidates: a
+// wave takes 0.11 per candidate, and per tile a full chip 0.005 + 0.0042 kCM
+// (the sub-blocks' share) + (2.3 + 0.5 kCM) 10^-5 per candidate by sub-blocks,
+// 2.5 10^-5 per candidate more and no such share by lanes.  Sub-blocks / lanes:
+// 2500 tiles, C = 1: 52 candidates 26 / 12, 208: 39 / 33, 416: 52 / 57; C = 8:
+// 52: 97 / 17, 416: 177 / 84; 323 tiles of 651, C = 8: 42 / 91; 64 of 231, C =
+// 4: 9 / 30; 5544 of 2, C = 8: 170 / 9.
+__host__ inline bool cells_by_lane(const TileLoad& t, int64_t tiles, int kCM) {
+  const double n = (double)tiles;
+  const double lanes = t.mean * n * (4.8e-5 + 0.5e-5 * kCM);
+  const double subs = n * (0.005 + 0.0042 * kCM) + t.mean * n * (2.3e-5 + 0.5e-5 * kCM);
+  return std::max(0.11 * t.most, lanes) < subs + 2.0;
 }
 
 // Whether a Gaussian plan's few-channel weights can take the short distance

@@ -24,6 +24,10 @@ constexpr uint64_t kPlanMagic = 0x48434750'4c414e31ull;  // "HCGPLAN1"
 constexpr int kTileX = 8;
 constexpr int kTileY = 8;
 constexpr int kTileCells = kTileX * kTileY;
+// Candidates of a plan's tiles: their mean, the largest.
+struct TileLoad {
+  double mean, most;
+};
 constexpr int kBlockCells = 16;  // cells of a gather block per side
 constexpr int kMaxRangesLimit = 1024;
 
@@ -201,12 +205,13 @@ struct hcg_plan_s {
   uint2* ranges;       // [ntiles][maxr] candidate ranges [a, b)
   uint32_t* nranges;   // [ntiles]
   uint32_t* ncand;     // [ntiles] candidates per tile
+  hcg::TileLoad load;
   // the same for blocks of 16 x 16 cells (gather_block.h); bmaxr = 0: none
   // (cells given by their centres, or more rings than the range table holds)
   int32_t bntx, bnty, bmaxr;
   uint2* branges;
   uint32_t* bnranges;
-  uint32_t* flags;     // [4] device status words
+  uint32_t* flags;     // device status words (plan.hip)
   double4* cells;      // [ny * nx] unit vectors of the cell centres (NaN: no cell)
 };
 

@@ -420,6 +420,12 @@ __global__ void __launch_bounds__(256) k_cell_vecs_arrays(const double* __restri
 // a5: candidate ranges per tile of output cells: ring_ranges (sphere.h) for
 // every ring that can hold a sample within R of the tile.
 // ---------------------------------------------------------------------------
+// A plan's status words: overflow, then from word 16 on kLoadSlots slots of a
+// line each, the largest and the sum of the candidate counts of their tiles.
+constexpr int kLoadSlots = 32;
+constexpr size_t kFlagBytes = 64 * (1 + kLoadSlots);
+constexpr int kHostWords = 8 + (int)kFlagBytes / 4;
+
 // One wave per tile; lane r handles ring i_lo + r (+64, ...).  Ranges are
 // written in ring order, two slots at most per ring.  The tile is the
 // lon/lat box [lon_a, lon_b] x [lat_a, lat_b] (radians) of its cells, or a
@@ -430,7 +436,8 @@ __device__ void tile_ranges_wave(const uint32_t* __restrict__ keys,
                                  int ring_last, uint32_t pix_base, double lon_a, double lon_b,
                                  double lat_a, double lat_b, double Rs, int maxr,
                                  uint2* __restrict__ out, uint32_t* nranges_out,
-                                 uint32_t* ncand_out, uint32_t* __restrict__ flags) {
+                                 uint32_t* ncand_out, uint32_t* __restrict__ load,
+                                 uint32_t* __restrict__ flags) {
   const int lane = threadIdx.x & 63;
   const double half_pi = 0.5 * kPi;
   const double sR = sin(0.5 * fmin(Rs, kPi));
@@ -469,6 +476,11 @@ __device__ void tile_ranges_wave(const uint32_t* __restrict__ keys,
   if (lane == 0) {
     *nranges_out = min(count, (uint32_t)maxr);
     if (ncand_out) *ncand_out = total;
+    if (load) {  // spread over the slots: all tiles on one address took 15 us
+      uint32_t* slot = load + 16 * (blockIdx.x % kLoadSlots);
+      atomicMax(slot, total);
+      atomicAdd((unsigned long long*)(slot + 2), (unsigned long long)total);
+    }
   }
 }
 
@@ -482,6 +494,7 @@ __device__ inline void tile_ranges_linear(const uint32_t* __restrict__ keys,
                                           uint2* __restrict__ ranges,
                                           uint32_t* __restrict__ nranges,
                                           uint32_t* __restrict__ ncand,
+                                          uint32_t* __restrict__ load,
                                           uint32_t* __restrict__ flags, uint32_t bx) {
   const int tile = (int)bx * 4 + (threadIdx.x >> 6);
   if (tile >= ntx * nty) return;
@@ -499,7 +512,7 @@ __device__ inline void tile_ranges_linear(const uint32_t* __restrict__ keys,
   const double Rs = support_rad * (1.0 + 1e-9) + 1e-12;
   tile_ranges_wave(keys, csr, ns, ring_first, ring_last, pix_base, lon_a, lon_b, lat_a, lat_b, Rs,
                    maxr, ranges + (int64_t)tile * maxr, &nranges[tile],
-                   ncand ? &ncand[tile] : nullptr, flags);
+                   ncand ? &ncand[tile] : nullptr, load, flags);
 }
 
 // Tiles of 8 x 8 cells, then (from block (ntx nty + 3) / 4 on) blocks of 16 x
@@ -517,10 +530,10 @@ __global__ void __launch_bounds__(256) k_tile_ranges(
   const uint32_t nt = (uint32_t)(ntx * nty + 3) / 4;
   if (blockIdx.x < nt)
     tile_ranges_linear(keys, csr, ns, ring_first, ring_last, pix_base, g, ntx, nty, kTileX,
-                       support_rad, maxr, ranges, nranges, ncand, flags, blockIdx.x);
+                       support_rad, maxr, ranges, nranges, ncand, flags + 16, flags, blockIdx.x);
   else
     tile_ranges_linear(keys, csr, ns, ring_first, ring_last, pix_base, g, br.ntx, br.nty,
-                       kBlockCells, support_rad, br.maxr, br.ranges, br.nranges, nullptr, flags,
+                       kBlockCells, support_rad, br.maxr, br.ranges, br.nranges, nullptr, nullptr, flags,
                        blockIdx.x - nt);
 }
 
@@ -587,7 +600,8 @@ __global__ void __launch_bounds__(256) k_tile_ranges_cap(
   // cell is within R + cap.z of it (triangle inequality); slack for rounding
   const double Rs = (support_rad + cap.z) * (1.0 + 1e-9) + 1e-12;
   tile_ranges_wave(keys, csr, ns, ring_first, ring_last, pix_base, cap.x, cap.x, cap.y, cap.y, Rs,
-                   maxr, ranges + (int64_t)tile * maxr, &nranges[tile], &ncand[tile], flags);
+                   maxr, ranges + (int64_t)tile * maxr, &nranges[tile], &ncand[tile], flags + 16,
+                   flags);
 }
 
 // ---------------------------------------------------------------------------
@@ -793,12 +807,12 @@ __global__ void __launch_bounds__(256) k_tile_ranges_fields(const PlanField* __r
   const uint32_t nt = (uint32_t)(F.ntx * F.nty + 3) / 4;
   if (lb < nt)
     tile_ranges_linear(F.keys, F.csr, F.nside, F.ring_first, F.ring_last, F.pix_base, F.grid, F.ntx,
-                       F.nty, kTileX, F.support_rad, F.maxr, F.ranges, F.nranges, F.ncand, F.flags,
-                       lb);
+                       F.nty, kTileX, F.support_rad, F.maxr, F.ranges, F.nranges, F.ncand, nullptr,
+                       F.flags, lb);
   else
     tile_ranges_linear(F.keys, F.csr, F.nside, F.ring_first, F.ring_last, F.pix_base, F.grid,
                        F.br.ntx, F.br.nty, kBlockCells, F.support_rad, F.br.maxr, F.br.ranges,
-                       F.br.nranges, nullptr, F.flags, lb - nt);
+                       F.br.nranges, nullptr, nullptr, F.flags, lb - nt);
 }
 #undef HCG_FIELD_BLOCK
 
@@ -1025,7 +1039,7 @@ struct PlanBuilder {
   double sigma = 0.0, fwhm_nominal = 0.0;
   int nside = 0;
   hipStream_t stream = nullptr;
-  uint32_t* host = nullptr;  // [0..7] pixel stats, [8..11] flags
+  uint32_t* host = nullptr;  // [0..7] pixel stats, [8 ..] flags
   int nx = 0, ny = 0, ntx = 0, nty = 0;
   int64_t ntiles = 0, ncell = 0;
   double R = 0.0;
@@ -1145,7 +1159,7 @@ struct PlanBuilder {
     const size_t o_nc = take(sizeof(uint32_t) * ntiles);
     const size_t o_brng = take(sizeof(uint2) * (size_t)bntx * bnty * bmaxr);
     const size_t o_bnr = take(sizeof(uint32_t) * (size_t)bntx * bnty);
-    const size_t o_flags = take(16);
+    const size_t o_flags = take(kFlagBytes);
     const size_t o_cells = take(sizeof(double4) * ncell);
     const size_t arena_bytes = off;
     if (arena.alloc_async(arena_bytes, stream) != hipSuccess) {
@@ -1217,7 +1231,7 @@ struct PlanBuilder {
     k_ring_csr<<<(unsigned)((nrings + 1 + 255) / 256), 256, 0, stream>>>(
         p->keys, n, nside, ring_first, nrings, pix_base, p->csr);
     HCG_LAUNCH_CHECK("k_ring_csr");
-    HCG_HIP(hipMemsetAsync(p->flags, 0, 16, stream));
+    HCG_HIP(hipMemsetAsync(p->flags, 0, kFlagBytes, stream));
     if (tg.grid) {
       const int64_t nblk = bmaxr ? (int64_t)bntx * bnty : 0;
       k_tile_ranges<<<(unsigned)((ntiles + 3) / 4 + (nblk + 3) / 4), 256, 0, stream>>>(
@@ -1231,13 +1245,20 @@ struct PlanBuilder {
           (int)ntiles, R, maxr, p->ranges, p->nranges, p->ncand, p->flags);
       HCG_LAUNCH_CHECK("k_tile_ranges_cap");
     }
-    HCG_HIP(hipMemcpyAsync(host + 8, p->flags, 16, hipMemcpyDeviceToHost, stream));
+    HCG_HIP(hipMemcpyAsync(host + 8, p->flags, kFlagBytes, hipMemcpyDeviceToHost, stream));
     return HCG_OK;
   }
 
   // after the flags have reached host[8..11]
   hcg_status finish(hcg_plan_t* out) {
     if (host[8]) return fail(HCG_E_DEVICE, "%s: candidate-range slots overflowed (internal bound)", who);
+    for (int k = 0; k < kLoadSlots; ++k) {
+      const uint32_t* slot = host + 8 + 16 + 16 * k;
+      uint64_t sum;
+      memcpy(&sum, slot + 2, 8);
+      p->load.most = std::max(p->load.most, (double)slot[0]);
+      p->load.mean += (double)sum / ((double)p->ntx * p->nty);
+    }
     p->arena_pooled = arena.async ? 1 : 0;
     p->arena = arena.release();
     plan_register(p);
@@ -1257,14 +1278,14 @@ hcg_status plan_build(hcg_plan_t* out, const double* lon_deg, const double* lat_
   thread_local bool tried = false;
   if (!tried) {
     tried = true;
-    if (hipHostMalloc((void**)&pinned, sizeof(uint32_t) * 16, hipHostMallocPortable) != hipSuccess) {
+    if (hipHostMalloc((void**)&pinned, sizeof(uint32_t) * kHostWords, hipHostMallocPortable) != hipSuccess) {
       (void)hipGetLastError();
       pinned = nullptr;
     }
   }
-  uint32_t stack_words[16] = {0};
+  uint32_t stack_words[kHostWords] = {0};
   uint32_t* host = pinned ? pinned : stack_words;
-  memset(host, 0, sizeof(uint32_t) * 16);
+  memset(host, 0, sizeof(uint32_t) * kHostWords);
   PlanBuilder b;
   hcg_status st = b.begin(lon_deg, lat_deg, n, tg, kernel, support_deg, opts, stream, host, who);
   if (st != HCG_OK) return st;
@@ -1578,6 +1599,10 @@ hcg_status plan_build_fields(int32_t nf, const hcg_field_desc* fd, const hcg_opt
     p->ranges = P.ranges;
     p->nranges = P.nranges;
     p->ncand = P.ncand;
+    for (const uint32_t c : (*ncand)[f]) {
+      p->load.most = std::max(p->load.most, (double)c);
+      p->load.mean += (double)c / ((double)P.ntx * P.nty);
+    }
     p->bntx = P.br.ntx;
     p->bnty = P.br.nty;
     p->bmaxr = P.br.maxr;

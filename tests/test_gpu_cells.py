@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2012_13173_amd as hcg
 import synth
 from tests.gridcheck import (assert_cube_close, assert_weights_close, gather_cells, sample_cells,
@@ -60,3 +61,47 @@ def test_few_channels_match_the_oracle(n, nchan, nx, ny, cell, fwhm, sigmas):
     torch.testing.assert_close(cube_m, cube, rtol=2e-7, atol=0, equal_nan=True)
     torch.testing.assert_close(W_m, W[None].expand_as(W_m), rtol=2e-7, atol=0)
     plan.destroy()
+
+
+# (n, C, nx, ny, cell', flags): tiles of two candidates and none; about one
+# chunk of 64; more than one
+LANE = [(400, 1, 203, 150, 2.0, False), (400, 7, 203, 150, 2.0, True),
+        (9000, 2, 190, 141, 1.2, False), (9000, 8, 190, 141, 1.2, True),
+        (26_000, 4, 262, 259, 0.9, False), (26_000, 5, 262, 259, 0.9, True)]
+
+
+@pytest.mark.parametrize("n,nchan,nx,ny,cell,flags", LANE)
+@pytest.mark.parametrize("fwhm", [3.0, 32.0])
+def test_tiles_of_few_candidates_match_the_oracle(n, nchan, nx, ny, cell, flags, fwhm):
+    """Maps whose tiles go to one wave each, alone and in a batch, against the
+    oracle: the same bounds."""
+    cell = cell * fwhm / 3.0
+    w = synth.small_cube(n=n, nchan=nchan, nx=nx, ny=ny, cell_arcmin=cell, fwhm_arcmin=fwhm,
+                         seed=1800 + nchan + nx)
+    spec = w.spectra.clone()
+    if flags:
+        spec[torch.rand(spec.shape, generator=torch.Generator().manual_seed(3)) < 0.1] = float("nan")
+    plan = hcg.hcg_plan(w.lon.to(DEV), w.lat.to(DEV), w.grid, w.fwhm_deg, w.support_deg)
+    cube = torch.full((nchan, ny, nx), 12345.0, device=DEV)
+    W = torch.full((nchan, ny, nx) if flags else (ny, nx), -1.0, device=DEV)
+    print(f"lanes n={n} C={nchan} {nx}x{ny} fwhm={fwhm}", flush=True)
+    (hcg.hcg_grid_masked if flags else hcg.hcg_grid)(plan, spec.to(DEV), cube, W)
+    torch.cuda.synchronize()
+    cells = np.concatenate(sample_cells(w.grid, seed=5, patches=5, patch=8))
+    iy, ix = np.divmod(cells, nx)
+    g = w.grid
+    cl = g.lon0 + (ix - (nx - 1) / 2) * g.dlon
+    cb = g.lat0 + (iy - (ny - 1) / 2) * g.dlat
+    V, Wr, _ = oracle.grid_points(w.lon.numpy(), w.lat.numpy(), spec.numpy(), cl, cb,
+                                  w.support_deg, oracle.Kernel.gauss(w.fwhm_deg), masked=flags)
+    idx = torch.from_numpy(cells).to(DEV)
+    assert_cube_close(cube.reshape(nchan, -1)[:, idx].cpu().numpy(), V.T, 1e-5, f"C={nchan}")
+    assert_weights_close(W.reshape(-1, nx * ny)[:, idx].cpu().numpy(),
+                         np.asarray(Wr).T if flags else np.asarray(Wr)[None])
+    if not flags:
+        batch = hcg.hcg_plan_batch([(w.lon.to(DEV), w.lat.to(DEV), g, w.fwhm_deg, w.support_deg)])
+        cube_b, W_b = torch.empty_like(cube), torch.empty_like(W)
+        hcg.hcg_grid_batch(batch, [spec.to(DEV)], [cube_b], [W_b])
+        torch.cuda.synchronize()
+        torch.testing.assert_close(cube_b, cube, rtol=1e-6, atol=1e-7, equal_nan=True)
+        torch.testing.assert_close(W_b, W, rtol=1e-6, atol=0)
