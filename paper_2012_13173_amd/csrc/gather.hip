@@ -81,6 +81,10 @@ constexpr int64_t kFewGroups = 1024;
 constexpr int64_t kFewBlocks = 512;
 
 
+// Most candidates of a tile with which any unflagged map of a narrow Gaussian
+// takes the independent waves.
+constexpr double kWaveCand = 240.0;
+
 // Which gather an FP32 map of more than 8 channels takes.  (Times in us of
 // tiles / independent waves / blocks; 0.5' cells and FWHM 3' unless said.)
 //   - Independent waves read a row once per cell block it reaches, up to 19
@@ -90,6 +94,12 @@ constexpr int64_t kFewBlocks = 512;
 //     20,000 x 1024 -> 400 x 400 of 1.2': 500 / 327 / 533, 100,000: 628 / 591 /
 //     753, 500,000: 1585 / 1778 / 1926.  Flagged, 2M x 64: 5790 / 2385 / 2514;
 //     x 256: 7525 / 8442 / 5190.
+//     The waves also win where a tile has few candidates, whatever the spectra's
+//     size (their products stay full): 23,600 x 2048 -> 436 x 436 (45 a tile)
+//     1176 / 768, 51,100 x 2048 -> 385 x 385 (110) 1034 / 768, 64,300 x 512 ->
+//     424 x 424 (110) 318 / 248; 73,600 x 512 -> 256 x 256 (350) 194 / 178 but
+//     99,700 x 2048 -> 329 x 329 (290) 1092 / 1145, 275,000 x 2048 -> 305 x 305
+//     (930) 2019 / 2242.
 //   - Blocks read a row 3.6 instead of 7.7 times and multiply at 2.7 times the
 //     FP32 matrix rate (flags cost them a third more products, the others
 //     twice as many), but in k-steps of 32 candidates, which a sparse map
@@ -110,7 +120,9 @@ F32Kernel f32_kernel(const hcg_plan_s* p, int64_t C, bool mask) {
                      !cached && (mask ? C > 64 && pairs >= 500.0 : C >= 512 && pairs >= 2000.0) &&
                      (int64_t)p->bntx * p->bnty * ((C + slab - 1) / slab) >= kFewBlocks;
   if (block) return F32Kernel::kBlock;
-  return C <= 128 || cached ? F32Kernel::kWave : F32Kernel::kTile;
+  const bool sparse = p->load.mean < kWaveCand && p->kern.type == kGauss && !mask &&
+                      support_chord2(p) < kNarrowChord2;
+  return C <= 128 || cached || sparse ? F32Kernel::kWave : F32Kernel::kTile;
 }
 
 template <int kForm, bool kPacked = false, bool kMask = false>
