@@ -576,8 +576,9 @@ hcg_status hcg_plan_batch(hcg_batch_t* out, int32_t nfields, const hcg_field_des
  *   data  host array [nfields] in the order given to hcg_plan_batch; fields
  *         may use different storage forms.
  * Every (field, tile, channel slab) is a work item.  Items are grouped by
- * kernel class (the few-channel FP32 gather, and the matrix-core gather of
- * each storage form, for rows read four elements or one at a time; a
+ * kernel class (the few-channel FP32 gathers, the three FP32 gathers of more
+ * channels, and the matrix-core gather of each other form, for rows read
+ * several elements or one at a time; a
  * BF16, FP16 x scale or FP8 x scale class takes 512-channel slabs at narrow
  * support only if every field's rows can be read eight at a time: nchan a
  * multiple of 8, spectra aligned to 8 elements); per
@@ -610,8 +611,9 @@ typedef struct {
   int32_t cost_order;        /* 1: items by decreasing cost; 0: by field, tile */
   int32_t tuned;             /* 1 once the configuration is fixed */
   int32_t graph_captured;    /* 1 once the launch is captured */
-  int32_t persistent_blocks; /* 256-thread workgroups of the persistent kernels (the
-                                C <= 8 class runs eight 64-thread ones for each) */
+  int32_t persistent_blocks; /* 256-thread workgroups of the persistent matrix-core
+                                kernels (few channels and independent waves: twice
+                                as many, or eight of 64 threads for each) */
   int64_t items;             /* work items of the last build */
   double tune_ms[8];         /* autotuner timings, persistent then work-item
                                 launch, each (256, cost), (512, cost),
