@@ -54,7 +54,8 @@ PAPER_CONTEXT = {"cpu_hours_per_TB": 21.0, "cpu_cores": 16,
 # the sources the gather kernels are compiled from: a traffic record taken on
 # other versions of them is not used
 GATHER_SRCS = [os.path.join(ROOT, "paper_2012_13173_amd", "csrc", f)
-               for f in ("gather.hip", "gather_tile.h", "sphere.h", "hcg_internal.h")]
+               for f in ("gather.hip", "gather_tile.h", "gather_block.hip", "gather_block.h",
+                         "sphere.h", "hcg_internal.h")]
 
 
 def gather_source_sha256():
@@ -722,8 +723,8 @@ def main():
         "pair_updates_per_s": stats["pairs"] * w.nchan / (grid_avg * 1e-3),
         "pairs": stats["pairs"],
         "candidates": stats["candidates"],
-        "roofline": {"kernel": "hcg::k_gather_mfma<0, 2, true, false, false, false, false> "
-                               "(FP32, 512-channel slabs, input order, narrow support)",
+        "roofline": {"kernel": "hcg::k_gather_block<2, true, false> (FP32 as three BF16 "
+                               "pieces, 256-channel slabs, input order, narrow support)",
                      "bound": "mfma", "achieved": achieved,
                      "peak": MFMA_FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / MFMA_FP32_PEAK_TFLOPS, "traffic": traffic,
