@@ -212,7 +212,9 @@ __device__ __forceinline__ void gather_block(const GatherArgs& a, int tile, int 
 
   // ---- staging: blocks of 64 candidates (two steps), by the waves in turn.
   // Padding past the last candidate takes the last one's row (see gather_tile)
-  // and a position beyond every cell.
+  // and a NaN position, within R of no cell and marked by no coarse test (a
+  // finite one in this frame is close to some cell more than 90 degrees from
+  // c).  In the FP64 product a candidate is a row of its own.
   auto cand = [&](uint32_t q) -> uint32_t {
     uint32_t lo = 0, hi = nrng - 1;
     while (lo < hi) {
@@ -239,12 +241,10 @@ __device__ __forceinline__ void gather_block(const GatherArgs& a, int tile, int 
     const bool in = 64u * blk + lane < total;
     const double* F = sm.frame;
     const double dx = nx - F[0], dy = ny - F[1], dz = nz - F[2];
-    double vx = dx * F[3] + dy * F[4] + dz * F[5];
-    double vy = dx * F[6] + dy * F[7] + dz * F[8];
+    const double vx = dx * F[3] + dy * F[4] + dz * F[5];
+    const double vy = dx * F[6] + dy * F[7] + dz * F[8];
     double vz = -0.5 * (dx * dx + dy * dy + dz * dz);
-    vx = in ? vx : 0.0;
-    vy = in ? vy : 0.0;
-    vz = in ? vz : -1e3;
+    vz = in ? vz : __builtin_nan("");
     sm.xyz[buf][0][lane] = vx;
     sm.xyz[buf][1][lane] = vy;
     sm.xyz[buf][2][lane] = vz;

@@ -271,14 +271,13 @@ __device__ __forceinline__ void gather_wave(const GatherArgs& a, int tile, int s
       }
     }
     if (count) {
-      // the last, partial batch: padded with candidates beyond every cell (on
-      // the first one's row)
+      // the last, partial batch: padded with candidates within R of no cell
+      // (NaN: any finite place in the chord's expanded form is close to some
+      // cell more than 90 degrees from c), on the first one's row
       const uint32_t at = (head + (uint32_t)lane) % kWaveQueue;
       const int64_t r0 = Q.row[head];
       if ((uint32_t)lane >= count) {
-        Q.x[at] = kGen ? 1e3 : 0.0;
-        Q.y[at] = 0.0;
-        Q.z[at] = kGen ? 0.0 : -1e3;
+        Q.x[at] = Q.y[at] = Q.z[at] = __builtin_nan("");
         Q.row[at] = r0;
       }
       batch((int)head, (int)((count + 3u) / 4u));
