@@ -108,6 +108,8 @@ constexpr double kWaveCand = 240.0;
 //     500,000 x 1024 -> 200 x 200 (2300): 4047 / 5094 / 3692; -> 400 x 400
 //     (570): 3734 / 4237 / 4061.  Flagged, 500,000 x 256 -> 400 x 400 (570):
 //     2081 / 2241 / 1744, 2M x 128 (2300): 7109 / 4299 / 3099.
+//     Their weights are split into pieces as well: supports of up to 11.7 sigma,
+//     whose weights (2^-100 at R) have three exact ones.
 F32Kernel f32_kernel(const hcg_plan_s* p, int64_t C, bool mask) {
   const bool cached = (double)p->n * (double)C * 4.0 <= 100e6;
   // pairs within R per cell if the samples cover the map evenly
@@ -116,12 +118,14 @@ F32Kernel f32_kernel(const hcg_plan_s* p, int64_t C, bool mask) {
   const double pairs =
       area > 0.0 ? (double)p->n * kPi * p->support_deg * p->support_deg / area : 0.0;
   const int64_t slab = mask ? kBlockSlabFlagged : kBlockSlab;
-  const bool block = p->bmaxr && p->kern.type == kGauss && support_chord2(p) < kNarrowChord2 &&
-                     !cached && (mask ? C > 64 && pairs >= 500.0 : C >= 512 && pairs >= 2000.0) &&
+  const double c2R = support_chord2(p);
+  const bool block = p->bmaxr && p->kern.type == kGauss && c2R < kNarrowChord2 &&
+                     p->kern.wscale * c2R * (1.0 + c2R) > -100.0 && !cached &&
+                     (mask ? C > 64 && pairs >= 500.0 : C >= 512 && pairs >= 2000.0) &&
                      (int64_t)p->bntx * p->bnty * ((C + slab - 1) / slab) >= kFewBlocks;
   if (block) return F32Kernel::kBlock;
   const bool sparse = p->load.mean < kWaveCand && p->kern.type == kGauss && !mask &&
-                      support_chord2(p) < kNarrowChord2;
+                      c2R < kNarrowChord2;
   return C <= 128 || cached || sparse ? F32Kernel::kWave : F32Kernel::kTile;
 }
 

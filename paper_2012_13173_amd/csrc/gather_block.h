@@ -10,13 +10,18 @@
 //     flags), the accumulators taking half of a CU's registers: wave w holds
 //     channels 32 w .. of all sixteen cell blocks;
 //   - FP32 operands are split into three BF16 pieces (round to nearest even:
-//     x = hi + mid + lo exactly, 24 bits) and multiplied by six
-//     v_mfma_f32_16x16x32_bf16 (hi.hi, hi.mid, mid.hi, mid.mid, hi.lo, lo.hi,
-//     smallest first).  The dropped terms are below 2^-26 of a product, the
-//     accumulator rounds once per 32 candidates instead of once per 4: the
-//     error against 64 bits is no larger than with v_mfma_f32_16x16x4_f32
-//     (largest per-channel relative L2 of the two maps below: 9.4e-7 and
-//     6.9e-7, both 1.2e-6 with that), at 2.7 times its rate;
+//     x = hi + mid + lo exactly, 24 bits, for |x| from 2^-110 to the largest
+//     BF16) and multiplied by six v_mfma_f32_16x16x32_bf16 (hi.hi, hi.mid,
+//     mid.hi, mid.mid, hi.lo, lo.hi, smallest first).  The dropped terms are
+//     below 2^-26 of a product, the accumulator rounds once per 32 candidates
+//     instead of once per 4: the error against 64 bits is no larger than with
+//     v_mfma_f32_16x16x4_f32 (largest per-channel relative L2 of the two maps
+//     below: 9.4e-7 and 6.9e-7, both 1.2e-6 with that), at 2.7 times its rate.
+//     BF16 has FP32's exponents, so below 2^-110 the last piece runs into the
+//     smallest number, 2^-133 (spectra of 1e-36 would be off by 3.7e-5): a
+//     block that meets such values runs a second time on values times 2^64
+//     and takes its small results from there; larger and non-finite values
+//     are dealt with in convert() as well;
 //   - squared chords come from v_mfma_f64_16x16x4_f64: with cells u and
 //     candidates v relative to the block's centre c in a frame whose third
 //     axis is c, |u - v|^2 = -2 ux vx - 2 uy vy - (2 + 2 uz) vz + |u - c|^2 with
@@ -30,10 +35,12 @@
 //     the other dealt to the waves; half of the waves multiply first and half
 //     prepare first, so that the two waves of a SIMD use different units.
 // It measured 59.4 -> 50.7 ms (9.12M samples x 1024 -> 600 x 600 of 0.5', FWHM
-// 3') and, flagged, 4.63 -> 3.02 ms (1.14M x 256 -> 300 x 300).  What
+// 3') and, flagged, 4.63 -> 3.05 ms (1.14M x 256 -> 300 x 300).  What
 // bounds it now: 20 ms of matrix and 21 ms of vector instructions, which the
 // two waves of a SIMD overlap only in part, and the barriers.
 #pragma once
+
+#include <type_traits>
 
 #include "gather_tile.h"
 
@@ -54,8 +61,11 @@ __device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
 __device__ __forceinline__ float bf16_lo(uint32_t d) { return __uint_as_float(d << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t d) { return __uint_as_float(d & 0xFFFF0000u); }
 
-// The three BF16 pieces of two floats.  *rest: a value that is NaN exactly
-// when a piece is not finite (a or b non-finite, or beyond the largest BF16).
+// The three BF16 pieces of two floats.  *rest: what the first two leave of a and
+// b together: NaN exactly when a piece is not finite (a or b non-finite, or
+// beyond the largest BF16); at most 2^-127 and not 0 where the third piece is
+// not exact (below 2^-110; larger values leave 0 or multiples of 2^-133 that it
+// holds).
 __device__ __forceinline__ void split3(float a, float b, uint32_t* hi, uint32_t* mid, uint32_t* lo,
                                        float* rest) {
   const uint32_t h = pk_bf16(a, b);
@@ -67,6 +77,9 @@ __device__ __forceinline__ void split3(float a, float b, uint32_t* hi, uint32_t*
   *lo = pk_bf16(a2, b2);
   *rest = a2 + b2;
 }
+
+// Passes over the candidates after the first: see gather_block's convert().
+constexpr int kPassSmall = 1, kPassPos = 2, kPassNeg = 3;
 
 // Fragments (cell block x k-step) of a group's weights in LDS, twice.
 constexpr int kSlots = 16;
@@ -84,6 +97,7 @@ struct BlockSmem {
   uint32_t pre[kMaxRangesLimit + 1];
   uint32_t nrng;
   uint32_t odd;                    // a non-finite value was left out of the products
+  uint32_t small;                  // a value's pieces were not exact
   uint32_t mark[2 * kRing];        // marked cell blocks of the staged k-steps
   double mean[8][4];
   double frame[12];                // c, e1, e2
@@ -200,8 +214,8 @@ __device__ __forceinline__ void gather_block(const GatherArgs& a, int tile, int 
     for (int k = 0; k < 9; ++k) sm.frame[k] = f[k];
   }
 
-  if (tid == 0) sm.odd = 0u;
-  int pass = 0;  // 1, 2: see products()
+  if (tid == 0) sm.odd = sm.small = 0u;
+  int pass = 0;  // kPassSmall, kPassPos, kPassNeg: see convert()
   floatx4 acc[kCB][kJ];
   floatx4 accw[kMask ? kCB : 1][kMask ? kJ : 1];  // flagged form: channel weight sums
   double wsum[kOwn];
@@ -352,10 +366,28 @@ __device__ __forceinline__ void gather_block(const GatherArgs& a, int tile, int 
 
   // the loaded rows as BF16 pieces (and flags)
   uint4 bh[kJ], bm[kJ], bl[kJ], fl[kMask ? kJ : 1];
-  auto convert = [&]() {
-    float rest = 0.f;
+  auto convert = [&](auto first) {
+    if constexpr (!first()) {
+      const uint32_t other = pass == kPassPos ? 0xFF800000u : 0x7F800000u;  // -inf, +inf
+#pragma unroll
+      for (int j = 0; j < kJ; ++j)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          const float x = raw[t][j];
+          const uint32_t u = __float_as_uint(x);
+          const bool fin = (u & 0x7F800000u) != 0x7F800000u;
+          // (a value that 2^64 takes past 2^127 stays finite: its cells keep
+          // what the first pass gave them)
+          const float big = __builtin_amdgcn_fmed3f(x * 0x1p64f, -0x1p127f, 0x1p127f);
+          raw[t][j] = pass == kPassSmall ? (fin ? big : kMask ? x : 0.f)
+                                         : (!fin && u != other ? 1.f : 0.f);
+        }
+    }
+    // rest of each channel: a small sum shows where no larger value's hides it
+    float rest[kJ];
 #pragma unroll
     for (int j = 0; j < kJ; ++j) {
+      rest[j] = 0.f;
       uint32_t h[4], m[4], l[4], k[4];
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
@@ -370,72 +402,66 @@ __device__ __forceinline__ void gather_block(const GatherArgs& a, int tile, int 
           vb = fb ? vb : 0.f;
         }
         split3(va, vb, &h[p], &m[p], &l[p], &r);
-        rest += r;
+        rest[j] += r;
       }
       bh[j] = make_uint4(h[0], h[1], h[2], h[3]);
       bm[j] = make_uint4(m[0], m[1], m[2], m[3]);
       bl[j] = make_uint4(l[0], l[1], l[2], l[3]);
       if constexpr (kMask) fl[j] = make_uint4(k[0], k[1], k[2], k[3]);
     }
-    // A value that is not finite, or beyond the largest BF16, has no such
-    // pieces.  Rare: those steps split by truncation (exact for every finite
-    // value) with the non-finite values left out; two further passes over
-    // the candidates then find the cells within R of a sample that is +inf
-    // or NaN, and -inf or NaN.
-    if (__builtin_expect(pass == 0 && __ballot(rest != rest) != 0ull, 0)) {
-      asm volatile("; split by truncation");  // keeps this out of the common path
-      bool lost = false;
+    // Values without exact pieces are rare.  One that is not finite, or beyond
+    // the largest BF16: those steps split by truncation (exact for every finite
+    // value from 2^-110 on) with the non-finite values left out; two further
+    // passes over the candidates (kPassPos, kPassNeg) then find the cells
+    // within R of a sample that is +inf or NaN, and -inf or NaN.  One below
+    // 2^-110: a further pass multiplies values times 2^64 (kPassSmall).
+    bool special = false;
+#pragma unroll
+    for (int j = 0; j < kJ; ++j) special |= __builtin_amdgcn_classf(rest[j], 0x093);  // NaN, subnormal
+    if (first() && __builtin_expect(__ballot(special) != 0ull, 0)) {
+      bool nan = false, tiny = false;
 #pragma unroll
       for (int j = 0; j < kJ; ++j) {
-        uint32_t H[4], M[4], L[4];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          H[p] = M[p] = L[p] = 0u;
-#pragma unroll
-          for (int e = 0; e < 2; ++e) {
-            const float x = raw[2 * p + e][j];
-            const bool fin = (__float_as_uint(x) & 0x7F800000u) != 0x7F800000u;
-            lost = lost || !fin;
-            const float v = fin ? x : 0.f;
-            const uint32_t hb = __float_as_uint(v) & 0xFFFF0000u;
-            const float r1 = v - __uint_as_float(hb);
-            const uint32_t mb = __float_as_uint(r1) & 0xFFFF0000u;
-            const uint32_t lb = __float_as_uint(r1 - __uint_as_float(mb)) & 0xFFFF0000u;
-            H[p] |= hb >> (e ? 0 : 16);
-            M[p] |= mb >> (e ? 0 : 16);
-            L[p] |= lb >> (e ? 0 : 16);
-          }
-        }
-        bh[j] = make_uint4(H[0], H[1], H[2], H[3]);
-        bm[j] = make_uint4(M[0], M[1], M[2], M[3]);
-        bl[j] = make_uint4(L[0], L[1], L[2], L[3]);
+        nan |= rest[j] != rest[j];
+        tiny |= __builtin_amdgcn_classf(rest[j], 0x090);
       }
-      if (!kMask && __ballot(lost) && lane == 0) sm.odd = 1u;
-    }
-    if constexpr (!kMask) {
-      if (__builtin_expect(pass > 0, 0)) {
-        asm volatile("; flags of non-finite values");
-        const uint32_t other = pass == 1 ? 0xFF800000u : 0x7F800000u;  // -inf, +inf
+      if (__ballot(tiny)) sm.small = 1u;
+      if (__ballot(nan)) {
+        asm volatile("; split by truncation");
+        bool lost = false;
 #pragma unroll
         for (int j = 0; j < kJ; ++j) {
-          uint32_t F[4];
+          uint32_t H[4], M[4], L[4];
 #pragma unroll
           for (int p = 0; p < 4; ++p) {
-            const uint32_t xa = __float_as_uint(raw[2 * p][j]);
-            const uint32_t xb = __float_as_uint(raw[2 * p + 1][j]);
-            F[p] = (((xa & 0x7F800000u) == 0x7F800000u && xa != other) ? 0x3F80u : 0u) |
-                   (((xb & 0x7F800000u) == 0x7F800000u && xb != other) ? 0x3F800000u : 0u);
+            H[p] = M[p] = L[p] = 0u;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const float x = raw[2 * p + e][j];
+              const bool fin = (__float_as_uint(x) & 0x7F800000u) != 0x7F800000u;
+              lost = lost || !fin;
+              const float v = fin ? x : 0.f;
+              const uint32_t hb = __float_as_uint(v) & 0xFFFF0000u;
+              const float r1 = v - __uint_as_float(hb);
+              const uint32_t mb = __float_as_uint(r1) & 0xFFFF0000u;
+              const uint32_t lb = __float_as_uint(r1 - __uint_as_float(mb)) & 0xFFFF0000u;
+              H[p] |= hb >> (e ? 0 : 16);
+              M[p] |= mb >> (e ? 0 : 16);
+              L[p] |= lb >> (e ? 0 : 16);
+            }
           }
-          bh[j] = make_uint4(F[0], F[1], F[2], F[3]);
-          bm[j] = bl[j] = make_uint4(0u, 0u, 0u, 0u);
+          bh[j] = make_uint4(H[0], H[1], H[2], H[3]);
+          bm[j] = make_uint4(M[0], M[1], M[2], M[3]);
+          bl[j] = make_uint4(L[0], L[1], L[2], L[3]);
         }
+        if (!kMask && __ballot(lost) && lane == 0) sm.odd = 1u;
       }
     }
   };
 
   // k-steps k .. kn - 1, whose weights are in buffer ab; starts the loads of
   // the next k-step
-  auto products = [&](uint32_t k, uint32_t kn, uint64_t bits, int ab) {
+  auto products = [&](uint32_t k, uint32_t kn, uint64_t bits, int ab, auto first) {
     // the weight sums of this wave's own cell blocks
 #pragma unroll
     for (int o = 0; o < kOwn; ++o) {
@@ -467,7 +493,7 @@ __device__ __forceinline__ void gather_block(const GatherArgs& a, int tile, int 
     };
 #pragma nounroll
     for (; k < kn; ++k) {
-      convert();
+      convert(first);
       load(k + 1);
       const uint32_t mask = (uint32_t)bits & ((1u << kCB) - 1u);
       bits >>= kCB;
@@ -493,7 +519,7 @@ __device__ __forceinline__ void gather_block(const GatherArgs& a, int tile, int 
     }
   };
 
-  for (;; ++pass) {
+  auto walk = [&](auto first) {
 #pragma unroll
     for (int cb = 0; cb < kCB; ++cb)
 #pragma unroll
@@ -535,7 +561,7 @@ __device__ __forceinline__ void gather_block(const GatherArgs& a, int tile, int 
         staged = k0 / 2 + kRing;
         k2 = k1;
         if (k1 < nk) k2 = group(k1, min(nk, known), &bits_n);
-        if (turn) products(k0, k1, bits, ab);
+        if (turn) products(k0, k1, bits, ab, first);
         if (k1 < k2) weights(k1, bits_n, ab ^ 1);
         for (; tested < upto; ++tested) coarse(tested);
         while (next < staged) {
@@ -543,7 +569,7 @@ __device__ __forceinline__ void gather_block(const GatherArgs& a, int tile, int 
           next += kWaves;
           fetch(next);
         }
-        if (!turn) products(k0, k1, bits, ab);
+        if (!turn) products(k0, k1, bits, ab, first);
         k0 = k1;
         k1 = k2;
         bits = bits_n;
@@ -559,7 +585,7 @@ __device__ __forceinline__ void gather_block(const GatherArgs& a, int tile, int 
       double w = wsum[o];
       w += __shfl_xor(w, 16);
       w += __shfl_xor(w, 32);
-      if (pass == 0 && cb < kCB && lane < 16) {
+      if (first() && cb < kCB && lane < 16) {
         sm.Wt[cb * 16 + lane] = w;
         const int x = x0 + (cb % kT) * 4 + (lane & 3), y = y0 + (cb / kT) * 4 + (lane >> 2);
         if (!kMask && a.wmap && slab == 0 && x < g.nx && y < g.ny)
@@ -569,9 +595,14 @@ __device__ __forceinline__ void gather_block(const GatherArgs& a, int tile, int 
     __syncthreads();
 
     const float qnan = __builtin_nanf("");
+    // (opaque, so that the addresses of the outputs are worked out here: made
+    // before the passes they would take the products' registers)
+    int row = y0 + lg;
+    int64_t chan = ch0;
+    asm volatile("" : "+v"(row), "+v"(chan));
 #pragma unroll
     for (int cb = 0; cb < kCB; ++cb) {
-      const int y = y0 + (cb / kT) * 4 + lg;
+      const int y = row + (cb / kT) * 4;
       const int x = x0 + (cb % kT) * 4;
       if (!live || y >= g.ny || x >= g.nx) continue;
       float inv[4];
@@ -586,19 +617,30 @@ __device__ __forceinline__ void gather_block(const GatherArgs& a, int tile, int 
       const bool full = x + 3 < g.nx;
 #pragma unroll
       for (int j = 0; j < kJ; ++j) {
-        const int64_t ch = ch0 + j;
+        const int64_t ch = chan + j;
         if (ch >= C) continue;
         float* dst = a.cube + ch * G + at;
-        if constexpr (!kMask) {
-          if (pass > 0) {
+        if (!first() && pass == kPassSmall) {
+          // results below 2^-100 (times 2^64 here), or whose sums are
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-              if (x + r < g.nx && acc[cb][j][r] > 0.f) {
-                const float inf = __builtin_inff();
-                dst[r] = pass == 1 ? inf : dst[r] == inf ? qnan : -inf;
-              }
-            continue;
+          for (int r = 0; r < 4; ++r) {
+            const float U = acc[cb][j][r];
+            float v;
+            if constexpr (kMask) v = U / accw[cb][j][r];
+            else v = has[r] ? U * inv[r] : qnan;
+            if (x + r < g.nx && (fabsf(U) < 0x1p-36f || fabsf(v) < 0x1p-36f) && v == v)
+              dst[r] = v * 0x1p-64f;
           }
+          continue;
+        }
+        if (!first()) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (x + r < g.nx && acc[cb][j][r] > 0.f) {
+              const float inf = __builtin_inff();
+              dst[r] = pass == kPassPos ? inf : dst[r] == inf ? qnan : -inf;
+            }
+          continue;
         }
         float v[4], wc[4];
 #pragma unroll
@@ -624,8 +666,17 @@ __device__ __forceinline__ void gather_block(const GatherArgs& a, int tile, int 
         }
       }
     }
-    if (kMask || pass == 2 || sm.odd == 0u) break;
+  };
+
+  // The further passes are code of their own: with their tests in one common
+  // loop the drift scan took 51.1 ms, so 50.4 (and 50.7 without passes for
+  // small values; flagged 3.11, 3.05 and 3.02).
+  walk(std::true_type{});
+  if (sm.small == 0u && (kMask || sm.odd == 0u)) return;
+  const bool odd = !kMask && sm.odd != 0u;
+  for (pass = sm.small ? kPassSmall : kPassPos; pass <= (odd ? kPassNeg : kPassSmall); ++pass) {
     __syncthreads();
+    walk(std::false_type{});
   }
 }
 
