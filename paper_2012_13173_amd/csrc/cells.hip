@@ -69,16 +69,20 @@ static void launch_cells_by_c(const GatherArgs& a, const TileLoad& load, hipStre
   else launch_cells_kernel<8, kMask, kWide, kGen>(a, load, stream);
 }
 
-// Values in the plan's order: out[p][c] = spec[perm[p]][c].
+// Values in the plan's order: out[p][c] = spec[perm[p]][c].  One value to a
+// thread, several where n C of them would be more threads than a launch holds.
+constexpr int64_t kSortBlocks = 1 << 22;
 __global__ void __launch_bounds__(256) k_sort_values(const float* __restrict__ spec,
                                                      const uint32_t* __restrict__ perm, int64_t n,
                                                      int C, float* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (C == 1) {
-    if (i < n) out[i] = spec[perm[i]];
-  } else if (i < n * C) {
-    const int64_t p = i / C;
-    out[i] = spec[(int64_t)perm[p] * C + (i - p * C)];
+  const int64_t step = (int64_t)gridDim.x * 256;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n * C; i += step) {
+    if (C == 1) {
+      out[i] = spec[perm[i]];
+    } else {
+      const int64_t p = i / C;
+      out[i] = spec[(int64_t)perm[p] * C + (i - p * C)];
+    }
   }
 }
 
@@ -92,22 +96,29 @@ hcg_status launch_cells(const hcg_plan_s* p, const float* spec, int C, float* cu
   GatherArgs a = plan_args(p);
   a.spec = spec;
   float* sorted = nullptr;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (may_alloc && p->n >= kCellsSortFrom &&
-      hipStreamIsCapturing(stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
-    hipMemPool_t pool = plan_pool();
+  if (may_alloc && p->n >= kCellsSortFrom) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool open = hipStreamIsCapturing(stream, &cap) == hipSuccess &&
+                      cap == hipStreamCaptureStatusNone;
+    hipMemPool_t pool = open ? plan_pool() : nullptr;
     const size_t bytes = sizeof(float) * (size_t)p->n * C;
-    if ((pool ? hipMallocFromPoolAsync((void**)&sorted, bytes, pool, stream)
+    if (open &&
+        (pool ? hipMallocFromPoolAsync((void**)&sorted, bytes, pool, stream)
               : hipMallocAsync((void**)&sorted, bytes, stream)) == hipSuccess) {
-      k_sort_values<<<(unsigned)((p->n * C + 255) / 256), 256, 0, stream>>>(spec, p->perm, p->n, C,
-                                                                           sorted);
+      k_sort_values<<<(unsigned)std::min((p->n * C + 255) / 256, kSortBlocks), 256, 0, stream>>>(
+          spec, p->perm, p->n, C, sorted);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) {
+        (void)hipFreeAsync(sorted, stream);
+        return fail(HCG_E_DEVICE, "launch of k_sort_values failed: %s", hipGetErrorString(e));
+      }
       a.spec = sorted;
       a.perm = nullptr;
     } else {
-      sorted = nullptr;  // no room: the values are read through the permutation
+      (void)hipGetLastError();
+      sorted = nullptr;  // capturing, or no room: the values are read through the permutation
     }
   }
-  (void)hipGetLastError();
   a.C = C;
   a.cube = cube;
   a.wmap = wmap;

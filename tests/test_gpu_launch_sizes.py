@@ -1,0 +1,59 @@
+"""Calls of more work-items than one dimension of a launch holds (2^32)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2012_13173_amd as hcg
+from tests.gridcheck import assert_cube_close, assert_weights_close
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+class Grid:
+    def __init__(self, nx, ny, lon0, lat0, dlon, dlat):
+        self.nx, self.ny, self.lon0, self.lat0, self.dlon, self.dlat = nx, ny, lon0, lat0, dlon, dlat
+
+
+def _need(gib):
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < gib * 2 ** 30:
+        pytest.skip(f"needs {gib} GiB of device memory")
+
+
+@pytest.fixture(autouse=True)
+def _give_back():
+    yield
+    torch.cuda.empty_cache()
+
+
+def test_few_channels_of_2_to_the_32_values():
+    """2^29 samples of eight channels: the values put into the plan's order
+    first are the ones read through its permutation."""
+    _need(120)
+    n, nchan = 1 << 29, 8
+    g = Grid(21, 13, 50.0, 20.0, 0.3, 0.3)
+    gen = torch.Generator(device=DEV).manual_seed(61)
+    lon = torch.rand(n, generator=gen, device=DEV, dtype=torch.float64) * 6.6 + 46.7
+    lat = torch.rand(n, generator=gen, device=DEV, dtype=torch.float64) * 4.2 + 17.9
+    plan = hcg.hcg_plan(lon, lat, g, 0.1, 0.12)
+    spec = torch.empty((n, nchan), device=DEV)
+    for c in range(nchan):
+        spec[:, c] = (lon * (c + 1)).sin()
+    del lon, lat
+    cube = torch.full((nchan, g.ny, g.nx), 12345.0, device=DEV)
+    W = torch.full((g.ny, g.nx), -1.0, device=DEV)
+    cube_p, W_p = torch.empty_like(cube), torch.empty_like(W)
+    print("2^32 values", flush=True)
+    hcg.hcg_grid(plan, spec, cube, W)
+    hcg.hcg_grid_noalloc(plan, spec, cube_p, W_p)
+    torch.cuda.synchronize()
+    plan.destroy()
+    assert torch.equal(cube.view(torch.int32), cube_p.view(torch.int32))
+    assert torch.equal(W.view(torch.int32), W_p.view(torch.int32))
+    # many thousand samples a cell: the mean of a smooth function of longitude
+    lon_c = g.lon0 + (torch.arange(g.nx, dtype=torch.float64) - 0.5 * (g.nx - 1)) * g.dlon
+    for c in range(nchan):
+        want = (lon_c * (c + 1)).sin()[None, :].expand(g.ny, g.nx)
+        assert (cube[c].cpu().double() - want).abs().max() < 0.2
