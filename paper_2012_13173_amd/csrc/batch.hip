@@ -71,13 +71,15 @@ constexpr int kCellsWaves = 4;
 template <int kCM>
 constexpr int kCellsParts = CellsShape<kCM, false>::kSubs / kCellsWaves;
 
-// One workgroup per item and part (blockIdx.y):
+// One workgroup per item and part (blockIdx.y; items past 2^21 in z, see
+// wide_grid):
 template <int kCM, bool kWide>
 __global__ void __launch_bounds__(256) k_cells_items(const GatherArgs* __restrict__ fields,
                                                      const BatchSeg* __restrict__ segs,
-                                                     uint32_t nseg) {
+                                                     uint32_t nseg, uint32_t nitems) {
   extern __shared__ __align__(32) unsigned char s_dyn[];
-  const uint32_t it = blockIdx.x;
+  const uint32_t it = blockIdx.z * gridDim.x + blockIdx.x;
+  if (it >= nitems) return;
   const BatchSeg sg = batch_seg_of(segs, nseg, it);
   const GatherArgs a = fields[sg.field];
   cells_tile<kCM, false, kWide, false>(a, (int)(it - sg.base), (int)blockIdx.y * kCellsWaves,
@@ -256,10 +258,13 @@ void launch_few_w(bool lane, const GatherArgs* fields, const BatchSeg* segs, uin
   using Sh = CellsShape<kCM, false>;
   const size_t lds =
       cells_lds_size<Sh::kNC, Sh::kS, false>(kCellsWaves, kCellsWaves, l.cells_maxr);
-  if (items)
-    k_cells_items<kCM, kWide><<<dim3(l.nitems, kCellsParts<kCM>), 256, lds, stream>>>(fields, segs, l.nseg);
-  else
+  if (items) {
+    const dim3 g = wide_grid(l.nitems);
+    k_cells_items<kCM, kWide>
+        <<<dim3(g.x, kCellsParts<kCM>, g.y), 256, lds, stream>>>(fields, segs, l.nseg, l.nitems);
+  } else {
     k_cells_batch<kCM, kWide><<<l.nblocks * 2, 256, lds, stream>>>(fields, segs, ctl);
+  }
 }
 
 template <int kCM>

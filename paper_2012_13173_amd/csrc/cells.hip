@@ -21,7 +21,8 @@ __global__ void __launch_bounds__((kCellsThreads<kCM, kWide>)) k_gather_cells(co
   extern __shared__ __align__(32) unsigned char s_dyn[];
   const int per_tile = CellsShape<kCM, kMask>::kSubs / subs;
   const int work = a.ntiles * per_tile;
-  const int w = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  const uint32_t b = wide_block();
+  const int w = (int)((b & 7) * (wide_blocks() >> 3) + (b >> 3));
   if (w >= work) return;
   const int tile = w / per_tile;
   cells_tile<kCM, kMask, kWide, kGen>(a, tile, (w - tile * per_tile) * subs, subs, nk, s_dyn);
@@ -58,7 +59,7 @@ static void launch_cells_kernel(const GatherArgs& a, const TileLoad& load, hipSt
   const int64_t work = all / subs;
   const size_t lds = cells_lds_size<Sh::kNC, Sh::kS, kGen>(subs * nk, subs, a.maxr);
   k_gather_cells<kCM, kMask, kWide, kGen>
-      <<<(unsigned)((work + 7) / 8 * 8), 64 * subs * nk, lds, stream>>>(a, subs, nk);
+      <<<wide_grid((work + 7) / 8 * 8), 64 * subs * nk, lds, stream>>>(a, subs, nk);
 }
 
 template <bool kMask, bool kWide, bool kGen>

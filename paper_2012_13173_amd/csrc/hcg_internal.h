@@ -282,6 +282,19 @@ struct BatchSeg {
 constexpr int kBatchXcds = 8;
 constexpr int kBatchCtl = 16;
 
+// Launches of one dimension that may have more than 2^32 work-items, which one
+// dimension of a dispatch cannot hold (16,384 x 16,384 cells are 4.2M tiles,
+// four workgroups of 256 for each at C = 5 .. 8): rows of 2^21 workgroups, of
+// up to 1024 threads.  The last row is whole, so a kernel has to leave out
+// what is past its work.
+inline dim3 wide_grid(int64_t blocks) {
+  constexpr int64_t kRow = 1 << 21;
+  return blocks <= kRow ? dim3((unsigned)blocks)
+                        : dim3((unsigned)kRow, (unsigned)((blocks + kRow - 1) / kRow));
+}
+__device__ __forceinline__ uint32_t wide_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
+__device__ __forceinline__ uint32_t wide_blocks() { return gridDim.y * gridDim.x; }
+
 // Gathers of FP32 spectra of more than 8 channels, by what a map and channel
 // count are faster with (f32_kernel, gather.hip): 8 x 8 tiles shared by a
 // workgroup (gather_tile.h), independent waves (gather_wave.h), 16 x 16-cell

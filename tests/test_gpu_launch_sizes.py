@@ -57,3 +57,41 @@ def test_few_channels_of_2_to_the_32_values():
     for c in range(nchan):
         want = (lon_c * (c + 1)).sin()[None, :].expand(g.ny, g.nx)
         assert (cube[c].cpu().double() - want).abs().max() < 0.2
+
+
+@pytest.mark.parametrize("side,n,nchan,batch", [(16384, 1700, 8, False), (32768, 420, 1, False),
+                                                (32768, 420, 1, True)])
+def test_few_channels_of_many_tiles(side, n, nchan, batch):
+    """4.2M tiles of four workgroups and 16.8M of one, every sample a candidate
+    of every tile (few enough to keep the test short, too many for one wave)."""
+    _need(130)
+    step = 0.25 / side
+    g = Grid(side, side, 120.0, 10.0, step, step)
+    rng = np.random.default_rng(62)
+    lon, lat = 120.0 + rng.uniform(-0.02, 0.02, n), 10.0 + rng.uniform(-0.02, 0.02, n)
+    spec = (rng.standard_normal((n, nchan)) + 2.0).astype(np.float32)
+    fwhm, support = 0.3, 0.3
+    dev = (torch.from_numpy(lon).to(DEV), torch.from_numpy(lat).to(DEV))
+    rows = torch.from_numpy(spec).to(DEV)
+    cube = torch.full((nchan, side, side), 12345.0, device=DEV)
+    W = torch.full((side, side), -1.0, device=DEV)
+    print(f"{side} x {side} C={nchan} batch={batch}", flush=True)
+    if batch:
+        b = hcg.hcg_plan_batch([(*dev, g, fwhm, support)], launch="items", nside=64)
+        hcg.hcg_grid_batch(b, [rows], [cube], [W])
+    else:
+        b = hcg.hcg_plan(*dev, g, fwhm, support, nside=64)
+        hcg.hcg_grid(b, rows, cube, W)
+    torch.cuda.synchronize()
+    b.destroy()
+    cells = np.concatenate([[0, side - 1, side * side - 1, side * (side - 1)],
+                            rng.integers(0, side * side, 60)])
+    iy, ix = np.divmod(cells, side)
+    cl = g.lon0 + (ix - 0.5 * (side - 1)) * g.dlon
+    cb = g.lat0 + (iy - 0.5 * (side - 1)) * g.dlat
+    V, Wr, _ = oracle.grid_points(lon, lat, spec, cl, cb, support, oracle.Kernel.gauss(fwhm))
+    idx = torch.from_numpy(cells).to(DEV)
+    assert_cube_close(cube.reshape(nchan, -1)[:, idx].cpu().numpy(), V.T, 1e-5, f"{side}")
+    assert_weights_close(W.reshape(-1)[idx].cpu().numpy(), Wr)
+    # and no cell left out
+    assert not bool((W < 0).any()) and not bool((cube == 12345.0).any())
