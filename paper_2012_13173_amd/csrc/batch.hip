@@ -78,7 +78,7 @@ __global__ void __launch_bounds__(256) k_cells_items(const GatherArgs* __restric
                                                      const BatchSeg* __restrict__ segs,
                                                      uint32_t nseg, uint32_t nitems) {
   extern __shared__ __align__(32) unsigned char s_dyn[];
-  const uint32_t it = blockIdx.z * gridDim.x + blockIdx.x;
+  const uint32_t it = (blockIdx.z << kWideRow) + blockIdx.x;
   if (it >= nitems) return;
   const BatchSeg sg = batch_seg_of(segs, nseg, it);
   const GatherArgs a = fields[sg.field];

@@ -21,9 +21,9 @@ __global__ void __launch_bounds__((kCellsThreads<kCM, kWide>)) k_gather_cells(co
   extern __shared__ __align__(32) unsigned char s_dyn[];
   const int per_tile = CellsShape<kCM, kMask>::kSubs / subs;
   const int work = a.ntiles * per_tile;
-  const uint32_t b = wide_block();
-  const int w = (int)((b & 7) * (wide_blocks() >> 3) + (b >> 3));
-  if (w >= work) return;
+  const int b = (int)wide_block(), eighth = (work + 7) >> 3;
+  const int w = (b & 7) * eighth + (b >> 3);
+  if ((b >> 3) >= eighth || w >= work) return;
   const int tile = w / per_tile;
   cells_tile<kCM, kMask, kWide, kGen>(a, tile, (w - tile * per_tile) * subs, subs, nk, s_dyn);
 }

@@ -287,13 +287,13 @@ constexpr int kBatchCtl = 16;
 // four workgroups of 256 for each at C = 5 .. 8): rows of 2^21 workgroups, of
 // up to 1024 threads.  The last row is whole, so a kernel has to leave out
 // what is past its work.
+constexpr int kWideRow = 21;
 inline dim3 wide_grid(int64_t blocks) {
-  constexpr int64_t kRow = 1 << 21;
-  return blocks <= kRow ? dim3((unsigned)blocks)
-                        : dim3((unsigned)kRow, (unsigned)((blocks + kRow - 1) / kRow));
+  constexpr int64_t row = (int64_t)1 << kWideRow;
+  return blocks <= row ? dim3((unsigned)blocks)
+                       : dim3((unsigned)row, (unsigned)((blocks + row - 1) / row));
 }
-__device__ __forceinline__ uint32_t wide_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
-__device__ __forceinline__ uint32_t wide_blocks() { return gridDim.y * gridDim.x; }
+__device__ __forceinline__ uint32_t wide_block() { return (blockIdx.y << kWideRow) + blockIdx.x; }
 
 // Gathers of FP32 spectra of more than 8 channels, by what a map and channel
 // count are faster with (f32_kernel, gather.hip): 8 x 8 tiles shared by a
