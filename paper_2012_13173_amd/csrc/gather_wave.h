@@ -138,17 +138,18 @@ __device__ __forceinline__ void gather_wave(const GatherArgs& a, int tile, int s
   }
   double wsum = 0.0;
 
-  // channels: kVec 64 h + 4 li + q, else 16 j + li, from c_w on; a lane past the
-  // last channel reads the row's first ones (those products are not stored)
+  // channels: kVec 64 h + 4 li + q, else 16 j + li, from c_w on (offsets from
+  // there fit 32 bits whatever the channel count); a lane past the last channel
+  // reads the slab's first ones (those products are not stored)
   const int64_t c_w = (int64_t)slab * (16 * kJ);
   const int jlive = (int)min<int64_t>(kJ, kVec ? (C - c_w + 63) / 64 * 4 : (C - c_w + 15) / 16);
   int32_t off[kH];
 #pragma unroll
   for (int h = 0; h < kH; ++h) {
     const int64_t ch = c_w + (kVec ? 64 * h + 4 * li : 16 * h + li);
-    off[h] = ch < C ? (int32_t)(4 * ch) : 0;
+    off[h] = ch < C ? (int32_t)(4 * (ch - c_w)) : 0;
   }
-  const char* spec = (const char*)a.spec;
+  const char* spec = (const char*)a.spec + 4 * c_w;
   float bb[kDepth][kJ];
   auto load = [&](int q0, int s, int set) {
     const char* rp = spec + Q.row[q0 + 4 * s + lg];

@@ -17,9 +17,9 @@ __global__ void __launch_bounds__(256, (kWaveOccupancy<kJ, kMask, kGen>)) k_gath
   // turn) take contiguous eighths of the cell blocks
   const int per_tile = 4 / subs;
   const int64_t work = (int64_t)a.ntiles * per_tile, eighth = (work + 7) / 8;
-  const int64_t slab = blockIdx.x / (8 * eighth), b = blockIdx.x - slab * 8 * eighth;
+  const int64_t at = wide_block(), slab = at / (8 * eighth), b = at - slab * 8 * eighth;
   const int64_t w = (b & 7) * eighth + (b >> 3);
-  if (w >= work) return;
+  if (w >= work || slab * (16 * kJ) >= a.C) return;
   const int tile = (int)(w / per_tile);
   gather_wave<kJ, kVec, kMask, kWide, kGen>(a, tile, (int)slab, (int)(w - (int64_t)tile * per_tile) * subs,
                                             subs, nk, s_dyn);
@@ -33,7 +33,7 @@ static hcg_status launch(const GatherArgs& a, int nk, hipStream_t stream) {
   if (blocks > INT32_MAX) return fail(HCG_E_UNSUPPORTED, "hcg_grid: too many channels");
   const size_t lds = wave_lds_bytes<kJ, kMask>(subs * nk, nk, a.maxr);
   k_gather_wave<kJ, kVec, kMask, kWide, kGen>
-      <<<(unsigned)blocks, 64 * subs * nk, lds, stream>>>(a, subs, nk);
+      <<<wide_grid(blocks), 64 * subs * nk, lds, stream>>>(a, subs, nk);
   HCG_LAUNCH_CHECK("k_gather_wave");
   return HCG_OK;
 }
@@ -104,9 +104,10 @@ __device__ __forceinline__ void wave_unit(const GatherArgs& a, uint32_t unit, ui
 template <int kJ, bool kVec, bool kWide>
 __global__ void __launch_bounds__(256, (kWaveOccupancy<kJ, false, false>)) k_wave_items(const GatherArgs* __restrict__ fields,
                                                        const BatchSeg* __restrict__ segs,
-                                                       uint32_t nseg) {
+                                                       uint32_t nseg, uint32_t nitems) {
   extern __shared__ __align__(16) unsigned char s_dyn[];
-  const uint32_t it = blockIdx.x;
+  const uint32_t it = wide_block();
+  if (it >= nitems) return;
   const BatchSeg sg = batch_seg_of(segs, nseg, it);
   const uint32_t local = it - sg.base;
   const GatherArgs a = fields[sg.field];
@@ -143,7 +144,7 @@ void launch_wave_items(int j, bool vec, bool wide, bool items, uint32_t blocks,
   do {                                                                                            \
     const size_t a = wave_lds_bytes<J, false>(4, 1, maxr), b = wave_lds_bytes<J, false>(4, 4, maxr); \
     const size_t lds = a > b ? a : b;                                                             \
-    if (items) k_wave_items<J, VEC, WIDE><<<blocks, 256, lds, stream>>>(fields, segs, nseg);      \
+    if (items) k_wave_items<J, VEC, WIDE><<<wide_grid(blocks), 256, lds, stream>>>(fields, segs, nseg, blocks); \
     else k_wave_batch<J, VEC, WIDE><<<blocks, 256, lds, stream>>>(fields, segs, ctl);             \
   } while (0)
 #define HCG_ITEMS_W(J, VEC)             \

@@ -95,3 +95,28 @@ def test_few_channels_of_many_tiles(side, n, nchan, batch):
     assert_weights_close(W.reshape(-1)[idx].cpu().numpy(), Wr)
     # and no cell left out
     assert not bool((W < 0).any()) and not bool((cube == 12345.0).any())
+
+
+@pytest.mark.parametrize("nchan", [2 ** 29 + 4, 2 ** 28 + 3])
+@pytest.mark.parametrize("launch", [None, "items", "persistent"])
+def test_one_cell_of_half_a_billion_channels(nchan, launch):
+    """2^24 workgroups and byte offsets past 2^31 within a row, rows read four
+    channels or one at a time: one sample, so V is the sample's spectrum."""
+    _need(12)
+    g = Grid(1, 1, 30.0, 40.0, 0.01, 0.01)
+    field = (torch.tensor([30.001], dtype=torch.float64, device=DEV),
+             torch.tensor([40.001], dtype=torch.float64, device=DEV), g, 0.05, 0.06)
+    plan = hcg.hcg_plan_batch([field], launch=launch) if launch else hcg.hcg_plan(*field)
+    spec = torch.empty((1, nchan), device=DEV)
+    spec.uniform_(1.0, 2.0, generator=torch.Generator(device=DEV).manual_seed(63))
+    cube = torch.full((nchan, 1, 1), 12345.0, device=DEV)
+    print(f"one cell C={nchan} {launch}", flush=True)
+    if launch:
+        hcg.hcg_grid_batch(plan, [spec], [cube])
+    else:
+        hcg.hcg_grid(plan, spec, cube)
+    torch.cuda.synchronize()
+    plan.destroy()
+    # w s / w: a product and a quotient rounded, the reciprocal too
+    worst = float((cube.view(-1) - spec.view(-1)).abs_().max())
+    assert worst <= 4 * 2.0 ** -23
