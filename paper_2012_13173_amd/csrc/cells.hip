@@ -16,7 +16,7 @@ namespace hcg {
 template <int kCM, bool kWide>
 constexpr int kCellsThreads = kCM <= 2 && !kWide ? 1024 : 512;
 
-template <int kCM, bool kMask, bool kWide, bool kGen>
+template <int kCM, bool kMask, bool kWide, bool kGen, bool kExact>
 __global__ void __launch_bounds__((kCellsThreads<kCM, kWide>)) k_gather_cells(const GatherArgs a, int subs, int nk) {
   extern __shared__ __align__(32) unsigned char s_dyn[];
   const int per_tile = CellsShape<kCM, kMask>::kSubs / subs;
@@ -25,7 +25,7 @@ __global__ void __launch_bounds__((kCellsThreads<kCM, kWide>)) k_gather_cells(co
   const int w = (b & 7) * eighth + (b >> 3);
   if ((b >> 3) >= eighth || w >= work) return;
   const int tile = w / per_tile;
-  cells_tile<kCM, kMask, kWide, kGen>(a, tile, (w - tile * per_tile) * subs, subs, nk, s_dyn);
+  cells_tile<kCM, kMask, kWide, kGen, kExact>(a, tile, (w - tile * per_tile) * subs, subs, nk, s_dyn);
 }
 
 template <int kCM, bool kMask, bool kWide, bool kGen>
@@ -42,7 +42,7 @@ __global__ void __launch_bounds__(64) k_gather_lane(const GatherArgs a) {
 // 5168 of 651, C = 8: 42 / 48 / 64 / 135; 1352 of 64,000, C = 4: 711 / 429 / 426
 // / 593; 400 of 866, C = 8: 18 / 13 / 11 / 17; C = 1, 5776 of 7100: 353 / 315 /
 // 312 / 344 / 448, 576 of 79,000: eight 629, sixteen 567.
-template <int kCM, bool kMask, bool kWide, bool kGen>
+template <int kCM, bool kMask, bool kWide, bool kGen, bool kExact>
 static void launch_cells_kernel(const GatherArgs& a, const TileLoad& load, hipStream_t stream) {
   if (cells_by_lane(load, a.ntiles, kCM)) {
     k_gather_lane<kCM, kMask, kWide, kGen>
@@ -58,16 +58,16 @@ static void launch_cells_kernel(const GatherArgs& a, const TileLoad& load, hipSt
   const int subs = nk >= 4 ? 1 : 4 / nk;
   const int64_t work = all / subs;
   const size_t lds = cells_lds_size<Sh::kNC, Sh::kS, kGen>(subs * nk, subs, a.maxr);
-  k_gather_cells<kCM, kMask, kWide, kGen>
+  k_gather_cells<kCM, kMask, kWide, kGen, kExact>
       <<<wide_grid((work + 7) / 8 * 8), 64 * subs * nk, lds, stream>>>(a, subs, nk);
 }
 
-template <bool kMask, bool kWide, bool kGen>
+template <bool kMask, bool kWide, bool kGen, bool kExact = false>
 static void launch_cells_by_c(const GatherArgs& a, const TileLoad& load, hipStream_t stream) {
-  if (a.C == 1) launch_cells_kernel<1, kMask, kWide, kGen>(a, load, stream);
-  else if (a.C == 2) launch_cells_kernel<2, kMask, kWide, kGen>(a, load, stream);
-  else if (a.C <= 4) launch_cells_kernel<4, kMask, kWide, kGen>(a, load, stream);
-  else launch_cells_kernel<8, kMask, kWide, kGen>(a, load, stream);
+  if (a.C == 1) launch_cells_kernel<1, kMask, kWide, kGen, kExact>(a, load, stream);
+  else if (a.C == 2) launch_cells_kernel<2, kMask, kWide, kGen, kExact>(a, load, stream);
+  else if (a.C <= 4) launch_cells_kernel<4, kMask, kWide, kGen, kExact>(a, load, stream);
+  else launch_cells_kernel<8, kMask, kWide, kGen, kExact>(a, load, stream);
 }
 
 // Values in the plan's order: out[p][c] = spec[perm[p]][c].  One value to a
@@ -127,7 +127,10 @@ hcg_status launch_cells(const hcg_plan_s* p, const float* spec, int C, float* cu
   // the circular Gaussian and the other kernel shapes are separate kernels,
   // so the common case carries no general weight path in its registers
   const bool gen = p->kern.type != kGauss, narrow = cells_narrow(a.c2R, p->kern);
-  if (mask) {
+  if (!centred_chords(p)) {
+    if (mask) launch_cells_by_c<true, true, true, true>(a, p->load, stream);
+    else launch_cells_by_c<false, true, true, true>(a, p->load, stream);
+  } else if (mask) {
     if (gen) launch_cells_by_c<true, true, true>(a, p->load, stream);
     else if (narrow) launch_cells_by_c<true, false, false>(a, p->load, stream);
     else launch_cells_by_c<true, true, false>(a, p->load, stream);

@@ -17,7 +17,9 @@
 //     |u - v|^2 = |u - c|^2 + |v - c|^2 - 2 (u - c).(v - c) is three FMAs per
 //     pair; the terms are of the size of the squared distances themselves,
 //     so nothing is lost to cancellation beyond a few units of the last
-//     place of (block + R)^2.
+//     place of (block + R)^2.  (Where that is not small beside R^2, see
+//     centred_chords, pairs pass with a margin for it and are then tested and
+//     weighted by the chord of the difference.)
 //   - No shared staging and no barrier inside the walk: each wave reads its
 //     candidates from global memory two chunks ahead (the four sub-blocks of
 //     a tile read the same lines), the values only of candidates inside the
@@ -134,8 +136,9 @@ __device__ __forceinline__ void cells_reduce(double (&v)[kN], int lane, int* at,
 // Sub-blocks [sub0, sub0 + subs) of a tile by blockDim.x / 64 waves, nk waves
 // for each (subs * nk = the waves): wave k of a sub-block takes every nk-th
 // chunk of 64 candidates.  kWide = false: squared support chord below 1e-4
-// and no weight below the normal floats (the launchers check both).
-template <int kCM, bool kMask, bool kWide, bool kGen>
+// and no weight below the normal floats (the launchers check both).  kExact:
+// cells too far apart for centred_chords.
+template <int kCM, bool kMask, bool kWide, bool kGen, bool kExact = false>
 __device__ inline void cells_tile(const GatherArgs& a, int tile, int sub0, int subs, int nk,
                                   unsigned char* base) {
   using Sh = CellsShape<kCM, kMask>;
@@ -185,7 +188,12 @@ __device__ inline void cells_tile(const GatherArgs& a, int tile, int sub0, int s
     for (int o = 1; o < kNC; o <<= 1) h2 = fmax(h2, __shfl_xor(h2, o));
     const bool any = __ballot(valid) != 0ull;
     if (lane < kNC) {
-      s_rec[sub * kNC + i] = valid ? CellsRec{-2.0 * ux, -2.0 * uy, -2.0 * uz, a.c2R - nu}
+      double thr = a.c2R - nu;
+      if constexpr (kExact) {  // t of a pair is off by at most 1.4e-15 of this square
+        const double all = sqrt(a.c2R) + 2.0 * sqrt(h2);
+        thr += 4e-15 * all * all;
+      }
+      s_rec[sub * kNC + i] = valid ? CellsRec{-2.0 * ux, -2.0 * uy, -2.0 * uz, thr}
                                    : CellsRec{0.0, 0.0, 0.0, -1e300};
       s_nu[sub * kNC + i] = nu;
       if constexpr (kGen)
@@ -283,10 +291,15 @@ __device__ inline void cells_tile(const GatherArgs& a, int tile, int sub0, int s
           const CellsRec m = s_rec[sub * kNC + i];
           const double t = fma(m.mx, d0.x, fma(m.my, d0.y, fma(m.mz, d0.z, nv0)));
           if (t <= m.thr) {
-            const double c2 = t + s_nu[sub * kNC + i];  // down to -1 ulp of nu where u = v
+            double c2 = t + s_nu[sub * kNC + i];  // down to -1 ulp of nu where u = v
             double w;
             if constexpr (kGen) {
               const CellsGenRec r = s_gen[sub * kNC + i];
+              if constexpr (kExact) {
+                const double dx = d0.x - r.ux, dy = d0.y - r.uy, dz = d0.z - r.uz;
+                c2 = fma(dx, dx, fma(dy, dy, dz * dz));
+                if (!(c2 <= a.c2R)) continue;
+              }
               w = pair_weight_gen(a.kern, fmax(c2, 0.0), d0.x - r.ux, d0.y - r.uy, d0.z - r.uz, r.f);
             } else if constexpr (kWide) {
               w = pair_weight64(c2, a.kern.wscale);

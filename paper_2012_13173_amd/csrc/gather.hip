@@ -110,7 +110,10 @@ constexpr double kWaveCand = 240.0;
 //     2081 / 2241 / 1744, 2M x 128 (2300): 7109 / 4299 / 3099.
 //     Their weights are split into pieces as well: supports of up to 11.7 sigma,
 //     whose weights (2^-100 at R) have three exact ones.
+//   - The tiles take a Gaussian's chords from the pair itself; the other two from
+//     offsets to the middle of a block (centred_chords).
 F32Kernel f32_kernel(const hcg_plan_s* p, int64_t C, bool mask) {
+  if (p->kern.type == kGauss && !centred_chords(p)) return F32Kernel::kTile;
   const bool cached = (double)p->n * (double)C * 4.0 <= 100e6;
   // pairs within R per cell if the samples cover the map evenly
   const double cells = (double)p->grid.nx * p->grid.ny;

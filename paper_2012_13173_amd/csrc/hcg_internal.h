@@ -193,6 +193,7 @@ struct hcg_plan_s {
   hcg::GridGeom grid;
   int32_t centres;     // 1: cells given by their centres (no linear geometry)
   double fwhm_deg, support_deg, sigma_rad, support_rad;
+  double tile_span;    // largest distance between two cells of a tile, at most
   hcg::KernelParams kern;
   int32_t ntx, nty, maxr;
   void* arena;
@@ -246,7 +247,8 @@ struct GatherArgs {
   int64_t C;
   GridGeom g;
   int ntx, ntiles, tiles_per_xcd;
-  int vec;  // rows can be read 4 elements at a time
+  int vec;  // rows can be read 4 elements at a time (independent waves of a batch: waves
+            // of a cell block)
   double c2R;     // squared chord of the support radius, 4 sin^2(R / 2)
   float* cube;
   float* wmap;

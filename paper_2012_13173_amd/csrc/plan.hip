@@ -875,6 +875,13 @@ static int bit_length(uint32_t v) {
   return b;
 }
 
+// Largest distance between two cells of an 8 x 8 tile of a linear grid, at most
+// (radians).
+static double linear_tile_span(int nx, int ny, double dlon_deg, double dlat_deg) {
+  return kDeg2Rad * std::hypot((std::min(nx, kTileX) - 1) * dlon_deg,
+                               (std::min(ny, kTileY) - 1) * dlat_deg);
+}
+
 // Candidate-range slots of a 16 x 16-cell block (two per ring of its latitude
 // span + 2R), or 0 where the gather's range table has no room for them.
 static int block_max_ranges(double dlat_rad, double R, int nside) {
@@ -1169,15 +1176,16 @@ struct PlanBuilder {
 
     // candidate-range slots per tile: rings in the tile's latitude span + 2R,
     // two ranges per ring; rings are at least 2/(3 Ns) apart in latitude
-    double tile_span = 0.0;
+    double lat_span = 0.0, tile_span = 0.0;
     if (tg.grid) {
-      tile_span = (kTileY - 1) * std::fabs(tg.grid->dlat_deg) * kDeg2Rad;
+      lat_span = (kTileY - 1) * std::fabs(tg.grid->dlat_deg) * kDeg2Rad;
+      tile_span = linear_tile_span(nx, ny, tg.grid->dlon_deg, tg.grid->dlat_deg);
     } else {
       double rmax = 0.0;
       memcpy(&rmax, &hs[4], sizeof(double));
-      tile_span = 2.0 * std::min(rmax, kPi);
+      lat_span = tile_span = 2.0 * std::min(rmax, kPi);
     }
-    const double rings_d = (tile_span + 2.0 * R) / (2.0 / (3.0 * nside)) + 6.0;
+    const double rings_d = (lat_span + 2.0 * R) / (2.0 / (3.0 * nside)) + 6.0;
     if (rings_d > kMaxRangesLimit / 2)
       return fail(HCG_E_UNSUPPORTED,
                   "%s: support or tile too wide for nside %d (%.0f rings per tile; at most %d)", who,
@@ -1235,6 +1243,7 @@ struct PlanBuilder {
     p->support_deg = support_deg;
     p->sigma_rad = sigma;
     p->support_rad = R;
+    p->tile_span = tile_span;
     p->kern = kp;
     p->ntx = ntx;
     p->nty = nty;
@@ -1629,6 +1638,7 @@ hcg_status plan_build_fields(int32_t nf, const hcg_field_desc* fd, const hcg_opt
     p->support_deg = fd[f].support_deg;
     p->sigma_rad = sigma[f];
     p->support_rad = P.support_rad;
+    p->tile_span = linear_tile_span(P.grid.nx, P.grid.ny, P.grid.dlon, P.grid.dlat);
     p->kern = kp[f];
     p->ntx = P.ntx;
     p->nty = P.nty;

@@ -206,6 +206,15 @@ inline double support_chord2(const hcg_plan_s* p) {
 }
 inline double weight_scale(const hcg_plan_s* p) { return p->kern.wscale; }
 
+// Whether squared chords may be made from the cell's and the sample's offsets to
+// the middle c of a block of cells, |u - c|^2 + |v - c|^2 - 2 (u - c).(v - c).  What
+// is rounded there has the size of (span + R)^2, not of R^2: an error of some
+// 1e-9 R^2 at 512 supports to a tile, and beyond (cells of 2 degrees with a
+// support of 0.02", or R = 0) pairs at R would be found wrong.
+inline bool centred_chords(const hcg_plan_s* p) {
+  return p->tile_span + 1e-12 <= 512.0 * p->support_rad;
+}
+
 // Gather arguments of a plan (the form, its pointers and the outputs are the
 // caller's).
 inline GatherArgs plan_args(const hcg_plan_s* p) {

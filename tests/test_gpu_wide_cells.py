@@ -128,3 +128,65 @@ def test_centres_scattered_over_the_sphere(kernel, support, flags):
     cube, W = _grid(plan, spec, flags, nchan, ny, nx)
     _check(cube, W, lon, lat, spec, cl, cb, support, make[1](*kernel[1:]), flags)
     plan.destroy()
+
+
+# ---------------------------------------------------------------------------
+# Cells far wider apart than the support: the squared distances of a pair are
+# tiny beside those to the middle of its block of cells.
+# ---------------------------------------------------------------------------
+POINTS = Grid(24, 20, 100.0, 0.0, 2.0, 2.0)
+
+
+@pytest.mark.parametrize("nchan", [1, 2, 4, 8, 12])
+@pytest.mark.parametrize("flags", [False, True])
+def test_support_of_zero_takes_the_samples_on_the_cells(nchan, flags):
+    """R = 0: a cell's sample, at exactly its centre, and no other; weight 1."""
+    g = POINTS
+    cl, cb = g.centres()
+    lon, lat = _samples_near(cl, cb, 200_000, 0.9, 48)
+    lon = np.concatenate([cl, lon])
+    lat = np.concatenate([cb, lat])
+    n = len(lon)
+    spec = _spectra(n, nchan, flags, 49)
+    field = (torch.from_numpy(lon).to(DEV), torch.from_numpy(lat).to(DEV), g, 0.05, 0.0)
+    plan = hcg.hcg_plan(*field, nside=64)
+    print(f"support 0 C={nchan} flags={flags}", flush=True)
+    cube, W = _grid(plan, spec, flags, nchan, g.ny, g.nx)
+    want = spec[:len(cl)].T.reshape(nchan, g.ny, g.nx)
+    np.testing.assert_array_equal(cube.cpu().numpy(), want)
+    np.testing.assert_array_equal(W.cpu().numpy(), np.isfinite(want).astype(np.float32)
+                                  if flags else np.ones((g.ny, g.nx), np.float32))
+    plan.destroy()
+    if not flags:
+        for launch in ("persistent", "items"):
+            batch = hcg.hcg_plan_batch([field], launch=launch, nside=64)
+            cube.fill_(12345.0)
+            W.fill_(-1.0)
+            hcg.hcg_grid_batch(batch, [torch.from_numpy(spec).to(DEV)], [cube], [W])
+            np.testing.assert_array_equal(cube.cpu().numpy(), want)
+            np.testing.assert_array_equal(W.cpu().numpy(), np.ones((g.ny, g.nx), np.float32))
+
+
+@pytest.mark.parametrize("nchan", [1, 3, 8, 12])
+@pytest.mark.parametrize("flags", [False, True])
+@pytest.mark.parametrize("shape", ["gauss", "elliptic"])
+def test_support_far_below_the_cells(nchan, flags, shape):
+    """Cells of 2 degrees, a support of 0.02 arcsec: 3.6e5 times less."""
+    g = POINTS
+    cl, cb = g.centres()
+    fwhm, support, n = 0.016 / 3600, 0.02 / 3600, 120_000
+    lon, lat = _samples_near(cl, cb, n, 1.1 * support, 50)
+    spec = _spectra(n, nchan, flags, 51)
+    dev = (torch.from_numpy(lon).to(DEV), torch.from_numpy(lat).to(DEV))
+    if shape == "gauss":
+        plan = hcg.hcg_plan(*dev, g, fwhm, support, nside=64)
+        kern = oracle.Kernel.gauss(fwhm)
+    else:
+        plan = hcg.hcg_plan_ex(*dev, hcg.Kernel.elliptic(fwhm, 0.7 * fwhm, 30.0), support, grid=g,
+                               nside=64)
+        kern = oracle.Kernel.elliptic(fwhm, 0.7 * fwhm, 30.0)
+    print(f"tiny support C={nchan} flags={flags} {shape}", flush=True)
+    cube, W = _grid(plan, spec, flags, nchan, g.ny, g.nx)
+    cells = np.arange(0, len(cl), 7)
+    _check(cube, W, lon, lat, spec, cl, cb, support, kern, flags, cells)
+    plan.destroy()
