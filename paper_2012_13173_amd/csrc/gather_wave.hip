@@ -16,12 +16,12 @@ __global__ void __launch_bounds__(256, (kWaveOccupancy<kJ, kMask, kGen>)) k_gath
   // one slab after the other; within one, the XCDs (workgroups go to them in
   // turn) take contiguous eighths of the cell blocks
   const int per_tile = 4 / subs;
-  const int64_t work = (int64_t)a.ntiles * per_tile, eighth = (work + 7) / 8;
-  const int64_t at = wide_block(), slab = at / (8 * eighth), b = at - slab * 8 * eighth;
-  const int64_t w = (b & 7) * eighth + (b >> 3);
-  if (w >= work || slab * (16 * kJ) >= a.C) return;
-  const int tile = (int)(w / per_tile);
-  gather_wave<kJ, kVec, kMask, kWide, kGen>(a, tile, (int)slab, (int)(w - (int64_t)tile * per_tile) * subs,
+  const uint32_t work = (uint32_t)a.ntiles * per_tile, eighth = (work + 7) / 8;
+  const uint32_t at = wide_block(), slab = __builtin_amdgcn_readfirstlane(at / (8 * eighth));
+  const uint32_t b = at - slab * 8 * eighth, w = (b & 7) * eighth + (b >> 3);
+  if (w >= work || (int64_t)slab * (16 * kJ) >= a.C) return;
+  const int tile = __builtin_amdgcn_readfirstlane(w / per_tile);
+  gather_wave<kJ, kVec, kMask, kWide, kGen>(a, tile, (int)slab, (int)(w - tile * per_tile) * subs,
                                             subs, nk, s_dyn);
 }
 
