@@ -80,6 +80,8 @@ constexpr int64_t kFewGroups = 1024;
 // Fewest workgroups of the block gather (one per CU, two rounds).
 constexpr int64_t kFewBlocks = 512;
 
+// Workgroups of the 8 x 8 tiles that fill the chip (two on a CU, four rounds).
+constexpr int64_t kFullTiles = 2048;
 
 // Most candidates of a tile with which any unflagged map of a narrow Gaussian
 // takes the independent waves.
@@ -100,6 +102,14 @@ constexpr double kWaveCand = 240.0;
 //     424 x 424 (110) 318 / 248; 73,600 x 512 -> 256 x 256 (350) 194 / 178 but
 //     99,700 x 2048 -> 329 x 329 (290) 1092 / 1145, 275,000 x 2048 -> 305 x 305
 //     (930) 2019 / 2242.
+//     Spectra in the caches, of more than 128 channels, and tiles to fill the
+//     chip several times: the tiles lose nothing by their fill, and the waves'
+//     weights, made anew for each 128 or 256 channels, count where they cost more
+//     (FWHM 3', cells of 1.5', 400 x 400; candidates of a tile in brackets):
+//     elliptical x 200 [6] 77 / 97, [178] 256 / 272, x 1024 [18] 364 / 482;
+//     tapered sinc x 200 [6] 79 / 93, [56] 135 / 122; flagged x 200 [6] 82 / 103,
+//     [53] 139 / 152, [178] 297 / 295; unflagged x 200 [6] 60 / 70, [56] 91 / 84,
+//     x 256 [6] 72 / 76, x 1024 [6] 483 / 360.
 //   - Blocks read a row 3.6 instead of 7.7 times and multiply at 2.7 times the
 //     FP32 matrix rate (flags cost them a third more products, the others
 //     twice as many), but in k-steps of 32 candidates, which a sparse map
@@ -127,7 +137,15 @@ F32Kernel f32_kernel(const hcg_plan_s* p, int64_t C, bool mask) {
                      (mask ? C > 64 && pairs >= 500.0 : C >= 512 && pairs >= 2000.0) &&
                      (int64_t)p->bntx * p->bnty * ((C + slab - 1) / slab) >= kFewBlocks;
   if (block) return F32Kernel::kBlock;
-  const bool sparse = p->load.mean < kWaveCand && p->kern.type == kGauss && !mask &&
+  const double load = p->load.mean;
+  const int64_t tiles = (int64_t)p->ntx * p->nty;
+  if (C > 128 && tiles * ((C + 255) / 256) >= kFullTiles &&
+      (p->kern.type == kElliptic   ? true
+       : p->kern.type == kSinc     ? mask || load < 40.0
+       : mask                      ? load < 150.0
+                                   : load < 20.0 && C <= 256))
+    return F32Kernel::kTile;
+  const bool sparse = load < kWaveCand && p->kern.type == kGauss && !mask &&
                       c2R < kNarrowChord2;
   return C <= 128 || cached || sparse ? F32Kernel::kWave : F32Kernel::kTile;
 }

@@ -1,5 +1,5 @@
 // Launches of the independent-wave gather (gather_wave.h) on one plan.
-#include <cmath>
+#include <algorithm>
 
 #include "batch_items.h"
 #include "gather_wave.h"
@@ -71,18 +71,27 @@ hcg_status launch_wave(const hcg_plan_s* p, const float* spec, int64_t C, float*
 #undef HCG_WAVE
 }
 
-// Channels of a wave and waves of a cell block.  Wide slabs compute the
-// weights less often; a map of few cell blocks takes narrower ones, then
-// several waves to a cell block, until there are kWaveFew waves (four per SIMD:
-// 20,000 samples x 67 channels -> 45 x 37, 120 cell blocks: 335 us with one
-// workgroup per 8 x 8 tile, 42 us so).
-constexpr int64_t kWaveFew = 4096;
+// Channels of a wave and waves of a cell block (times in us, 0.5' to 1.5' cells,
+// FWHM 3').  Wide slabs compute the weights less often; 256 channels leave half
+// of the waves of 128, so they are for maps that have kWaveFew waves all the
+// same (four per SIMD), and not for the elliptical weights, whose registers
+// spill there (200 channels -> 150 x 150, 1444 cell blocks: 82 with 128
+// channels a wave, 92 with 256; 120 with 64).  A map of very few takes 64
+// channels, and so does a flagged circular Gaussian one, whose weights cost
+// least (1444 blocks: 46, 50 with 128).  Four waves to a cell block shorten its
+// walk where few cell blocks have many candidates (20,000 x 67 -> 45 x 37: 335
+// with one workgroup per 8 x 8 tile, 42 so; 1444 blocks, elliptical, 128
+// channels: 1150 candidates a tile 140 with one, 128 with four; 115: 28 and 49).
+constexpr int64_t kWaveFew = 4096, kWaveVeryFew = 256;
 WaveShape wave_shape(const hcg_plan_s* p, int64_t C, bool vec, bool mask) {
   const int64_t blocks = 4 * (int64_t)p->ntx * p->nty;
-  int j = C <= 64 ? 4 : C <= 128 || mask || !vec ? 8 : 16;
-  while (j > 4 && blocks * ((C + 16 * j - 1) / (16 * j)) < kWaveFew) j /= 2;
-  const int nk = blocks * ((C + 16 * j - 1) / (16 * j)) < kWaveFew ? 4 : 1;
-  return WaveShape{j, nk};
+  auto waves = [&](int j) { return blocks * ((C + 16 * j - 1) / (16 * j)); };
+  int j = C <= 64 ? 4 : C <= 128 || mask || !vec || p->kern.type == kElliptic ? 8 : 16;
+  if (j == 16 && waves(j) < kWaveFew) j = 8;
+  const int64_t least = mask && p->kern.type == kGauss ? kWaveFew : kWaveVeryFew;
+  if (j == 8 && waves(j) < least) j = 4;
+  const bool split = waves(j) < kWaveFew && p->load.most >= std::max(128.0, 0.6 * (double)waves(j));
+  return WaveShape{j, split ? 4 : 1};
 }
 
 // ---------------------------------------------------------------------------
