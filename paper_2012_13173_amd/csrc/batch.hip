@@ -316,7 +316,7 @@ hcg_status launch_class(int cls, int qw, bool wide, const GatherArgs* fields,
 // Kernel class of a field's data (vec: rows read four elements at a time).
 int field_class(const hcg_plan_s* p, const hcg_field_data& d, bool vec) {
   if (d.dtype == HCG_F32 && d.nchan <= 8)
-    return cells_by_lane(p->load, (int64_t)p->ntx * p->nty, d.nchan == 1 ? 1 : 8) ||
+    return cells_by_lane(p, d.nchan == 1 ? 1 : 8, false) ||
                    !centred_chords(p)  // the lanes' chords are those of the pairs
                ? (d.nchan == 1 ? kClsLane : kClsLane8)
                : (d.nchan == 1 ? kClsCells : kClsCells8);

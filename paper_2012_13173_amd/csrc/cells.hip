@@ -19,7 +19,7 @@ constexpr int kCellsThreads = kCM <= 2 && !kWide ? 1024 : 512;
 template <int kCM, bool kMask, bool kWide, bool kGen, bool kExact>
 __global__ void __launch_bounds__((kCellsThreads<kCM, kWide>)) k_gather_cells(const GatherArgs a, int subs, int nk) {
   extern __shared__ __align__(32) unsigned char s_dyn[];
-  const int per_tile = CellsShape<kCM, kMask>::kSubs / subs;
+  const int per_tile = CellsShape<kCM, kMask, kGen>::kSubs / subs;
   const int work = a.ntiles * per_tile;
   const int b = (int)wide_block(), eighth = (work + 7) >> 3;
   const int w = (b & 7) * eighth + (b >> 3);
@@ -43,18 +43,18 @@ __global__ void __launch_bounds__(64) k_gather_lane(const GatherArgs a) {
 // / 593; 400 of 866, C = 8: 18 / 13 / 11 / 17; C = 1, 5776 of 7100: 353 / 315 /
 // 312 / 344 / 448, 576 of 79,000: eight 629, sixteen 567.
 template <int kCM, bool kMask, bool kWide, bool kGen, bool kExact>
-static void launch_cells_kernel(const GatherArgs& a, const TileLoad& load, hipStream_t stream) {
-  if (cells_by_lane(load, a.ntiles, kCM)) {
+static void launch_cells_kernel(const hcg_plan_s* p, const GatherArgs& a, hipStream_t stream) {
+  if (cells_by_lane(p, kCM, kMask)) {
     k_gather_lane<kCM, kMask, kWide, kGen>
         <<<(unsigned)a.tiles_per_xcd * 8u, 64, cells_lane_lds_size<kCM>(a.maxr), stream>>>(a);
     return;
   }
-  using Sh = CellsShape<kCM, kMask>;
+  using Sh = CellsShape<kCM, kMask, kGen>;
   const int64_t all = (int64_t)a.ntiles * Sh::kSubs;
   constexpr int kMost = kCellsThreads<kCM, kWide> / 64;
   constexpr int64_t kWaves = kCM == 1 ? 16384 : 4096;
   int nk = 1;
-  while (nk < kMost && all * nk * 2 <= kWaves && load.most >= 64.0 * 2 * (nk * 2)) nk *= 2;
+  while (nk < kMost && all * nk * 2 <= kWaves && p->load.most >= 64.0 * 2 * (nk * 2)) nk *= 2;
   const int subs = nk >= 4 ? 1 : 4 / nk;
   const int64_t work = all / subs;
   const size_t lds = cells_lds_size<Sh::kNC, Sh::kS, kGen>(subs * nk, subs, a.maxr);
@@ -63,11 +63,11 @@ static void launch_cells_kernel(const GatherArgs& a, const TileLoad& load, hipSt
 }
 
 template <bool kMask, bool kWide, bool kGen, bool kExact = false>
-static void launch_cells_by_c(const GatherArgs& a, const TileLoad& load, hipStream_t stream) {
-  if (a.C == 1) launch_cells_kernel<1, kMask, kWide, kGen, kExact>(a, load, stream);
-  else if (a.C == 2) launch_cells_kernel<2, kMask, kWide, kGen, kExact>(a, load, stream);
-  else if (a.C <= 4) launch_cells_kernel<4, kMask, kWide, kGen, kExact>(a, load, stream);
-  else launch_cells_kernel<8, kMask, kWide, kGen, kExact>(a, load, stream);
+static void launch_cells_by_c(const hcg_plan_s* p, const GatherArgs& a, hipStream_t stream) {
+  if (a.C == 1) launch_cells_kernel<1, kMask, kWide, kGen, kExact>(p, a, stream);
+  else if (a.C == 2) launch_cells_kernel<2, kMask, kWide, kGen, kExact>(p, a, stream);
+  else if (a.C <= 4) launch_cells_kernel<4, kMask, kWide, kGen, kExact>(p, a, stream);
+  else launch_cells_kernel<8, kMask, kWide, kGen, kExact>(p, a, stream);
 }
 
 // Values in the plan's order: out[p][c] = spec[perm[p]][c].  One value to a
@@ -128,16 +128,16 @@ hcg_status launch_cells(const hcg_plan_s* p, const float* spec, int C, float* cu
   // so the common case carries no general weight path in its registers
   const bool gen = p->kern.type != kGauss, narrow = cells_narrow(a.c2R, p->kern);
   if (!centred_chords(p)) {
-    if (mask) launch_cells_by_c<true, true, true, true>(a, p->load, stream);
-    else launch_cells_by_c<false, true, true, true>(a, p->load, stream);
+    if (mask) launch_cells_by_c<true, true, true, true>(p, a, stream);
+    else launch_cells_by_c<false, true, true, true>(p, a, stream);
   } else if (mask) {
-    if (gen) launch_cells_by_c<true, true, true>(a, p->load, stream);
-    else if (narrow) launch_cells_by_c<true, false, false>(a, p->load, stream);
-    else launch_cells_by_c<true, true, false>(a, p->load, stream);
+    if (gen) launch_cells_by_c<true, true, true>(p, a, stream);
+    else if (narrow) launch_cells_by_c<true, false, false>(p, a, stream);
+    else launch_cells_by_c<true, true, false>(p, a, stream);
   } else {
-    if (gen) launch_cells_by_c<false, true, true>(a, p->load, stream);
-    else if (narrow) launch_cells_by_c<false, false, false>(a, p->load, stream);
-    else launch_cells_by_c<false, true, false>(a, p->load, stream);
+    if (gen) launch_cells_by_c<false, true, true>(p, a, stream);
+    else if (narrow) launch_cells_by_c<false, false, false>(p, a, stream);
+    else launch_cells_by_c<false, true, false>(p, a, stream);
   }
   const hipError_t le = hipGetLastError();
   if (sorted) (void)hipFreeAsync(sorted, stream);

@@ -39,12 +39,15 @@ namespace hcg {
 
 // Weight sums per cell (one, or one per channel with flags), sums per cell,
 // and cells per sub-block: 16 sums of two registers per lane at C = 1, and
-// no more than about 80 registers of sums for any form but the flagged C = 8.
-template <int kCM, bool kMask>
+// no more than about 80 registers of sums for any form but the flagged C = 8
+// (whose 128 spilled beside the weights of the other kernel shapes, kGen: two
+// cells there, 300,000 samples x 8 -> 150 x 150, tapered sinc: 2231 us with
+// four, so 1111).
+template <int kCM, bool kMask, bool kGen = false>
 struct CellsShape {
   static constexpr int kW = kMask ? kCM : 1;
   static constexpr int kS = kCM + kW;
-  static constexpr int kNC = kS <= 2 ? 16 : kS <= 5 ? 8 : 4;
+  static constexpr int kNC = kS <= 2 ? 16 : kS <= 5 ? 8 : kGen && kS > 9 ? 2 : 4;
   static constexpr int kSubs = kTileCells / kNC;       // sub-blocks of a tile
   static constexpr int kSX = kNC == 16 ? 4 : kNC == 8 ? 4 : 2;  // cells of a sub-block in x
 };
@@ -141,7 +144,7 @@ __device__ __forceinline__ void cells_reduce(double (&v)[kN], int lane, int* at,
 template <int kCM, bool kMask, bool kWide, bool kGen, bool kExact = false>
 __device__ inline void cells_tile(const GatherArgs& a, int tile, int sub0, int subs, int nk,
                                   unsigned char* base) {
-  using Sh = CellsShape<kCM, kMask>;
+  using Sh = CellsShape<kCM, kMask, kGen>;
   constexpr int kNC = Sh::kNC, kW = Sh::kW, kS = Sh::kS, kSX = Sh::kSX, kSY = kNC / kSX;
   constexpr int kN = kNC * kS;
   static_assert(kN <= 64, "one sum per lane after the reduction");
@@ -451,26 +454,47 @@ __device__ inline void cells_lane(const GatherArgs& a, int tile, unsigned char* 
   }
 }
 
-// Whether a plan's tiles are taken by one wave each (cells_lane), kCM channels.
-// In us, fitted to 23 maps of 25 to 5544 tiles of 2 to 64,000 candidates: a
-// wave takes 0.11 per candidate, and per tile a full chip 0.005 + 0.0042 kCM
-// (the sub-blocks' share) + (2.3 + 0.5 kCM) 10^-5 per candidate by sub-blocks,
-// 2.5 10^-5 per candidate more and no such share by lanes.  Sub-blocks / lanes:
-// 2500 tiles, C = 1: 52 candidates 26 / 12, 208: 39 / 33, 416: 52 / 57; C = 8:
-// 52: 97 / 17, 416: 177 / 84; 323 tiles of 651, C = 8: 42 / 91; 64 of 231, C =
-// 4: 9 / 30; 5544 of 2, C = 8: 170 / 9.
-__host__ inline bool cells_by_lane(const TileLoad& t, int64_t tiles, int kCM) {
-  const double n = (double)tiles;
-  const double lanes = t.mean * n * (4.8e-5 + 0.5e-5 * kCM);
-  const double subs = n * (0.005 + 0.0042 * kCM) + t.mean * n * (2.3e-5 + 0.5e-5 * kCM);
-  return std::max(0.11 * t.most, lanes) < subs + 2.0;
-}
-
 // Whether a Gaussian plan's few-channel weights can take the short distance
 // series and the hardware exponential alone: narrow support, and the
 // exponent at R above the smallest normal float's.
 __host__ inline bool cells_narrow(double c2R, const KernelParams& k) {
   return c2R < kNarrowChord2 && k.wscale * c2R * (1.0 + c2R) > -125.0;
+}
+
+// Whether a plan's tiles are taken by one wave each (cells_lane), kCM channels.
+// In us: a wave takes `wave` per candidate; a full chip `lane` 1e-5 per candidate
+// of a tile by lanes, and by sub-blocks `tile` per tile (their frames and sums)
+// and `sub` 1e-5 per candidate, `walk` at least.  Circular Gaussian, fitted to 23 maps of 25 to
+// 5544 tiles of 2 to 64,000 candidates.  Sub-blocks / lanes: 2500 tiles, C = 1:
+// 52 candidates 26 / 12, 208: 39 / 33, 416: 52 / 57; C = 8: 52: 97 / 17, 416: 177
+// / 84; 323 tiles of 651, C = 8: 42 / 91; 64 of 231, C = 4: 9 / 30; 5544 of 2, C
+// = 8: 170 / 9; wide supports, C = 8 (whose sub-blocks keep two waves per SIMD),
+// 2500 tiles of 970: 592 / 371, of 4850: 2149 / 1684.  The other shapes' weights
+// cost several times as much, and by sub-blocks as the cells that a candidate
+// reaches, `hits` of a tile's; fitted to 192 maps of 25 to 2500 tiles: elliptical,
+// 2500 tiles, C = 1: 160 candidates 159 / 112, 300: 183 / 205, 1530: 584 / 896;
+// 361 tiles of 100, C = 8: 41 / 58; tapered sinc 47 / 78.
+__host__ inline bool cells_by_lane(const hcg_plan_s* p, int kCM, bool mask) {
+  const double n = (double)p->ntx * p->nty, sums = mask ? 2.0 * kCM : kCM + 1.0;
+  double wave = 0.11, lane = 4.8 + 0.5 * kCM;
+  double tile = 0.005 + 0.0042 * kCM, sub = 2.3 + 0.5 * kCM, walk = 2.0;
+  if (p->kern.type != kGauss) {
+    const double side = p->tile_span * 0.8, R = p->support_rad, reach = side + 2.0 * R;
+    const double hits = 3.9 * R * R / (reach * reach);
+    const double subs = sums <= 2.0 ? 4.0 : sums <= 5.0 ? 8.0 : sums <= 9.0 ? 16.0 : 32.0;
+    const bool sinc = p->kern.type == kSinc;
+    wave = (sinc ? 0.47 : 0.31) + 0.0085 * sums;
+    lane = (sinc ? 34.0 : 19.5) + 0.65 * sums;
+    tile = (sinc ? 0.0034 : 0.0023) * subs;
+    sub = (sinc ? 14.0 : 4.8) + 0.65 * sums + 31.0 * hits;
+    walk = 2.0 + 1.4 * sums;
+  } else if (kCM == 8 && !mask && !cells_narrow(support_chord2(p), p->kern)) {
+    wave = 0.2;
+    lane = 14.0;
+    sub = 18.0;
+  }
+  const double cand = 1e-5 * p->load.mean * n;
+  return std::max(wave * p->load.most, lane * cand) < tile * n + sub * cand + walk;
 }
 
 }  // namespace hcg
