@@ -105,3 +105,38 @@ def test_tiles_of_few_candidates_match_the_oracle(n, nchan, nx, ny, cell, flags,
         torch.cuda.synchronize()
         torch.testing.assert_close(cube_b, cube, rtol=1e-6, atol=1e-7, equal_nan=True)
         torch.testing.assert_close(W_b, W, rtol=1e-6, atol=0)
+
+
+# sub-blocks of two cells by several waves and by one; one wave to a tile
+@pytest.mark.parametrize("n,nx,ny,cell", [(20_000, 45, 37, 0.75), (60_000, 150, 141, 0.5),
+                                          (9000, 190, 141, 1.2)])
+@pytest.mark.parametrize("nchan", [5, 8])
+@pytest.mark.parametrize("shape", ["elliptic", "tapered_sinc"])
+def test_flagged_channels_of_the_other_kernel_shapes(n, nx, ny, cell, nchan, shape):
+    w = synth.small_cube(n=n, nchan=nchan, nx=nx, ny=ny, cell_arcmin=cell, seed=1900 + nchan + nx)
+    spec = w.spectra.clone()
+    spec[torch.rand(spec.shape, generator=torch.Generator().manual_seed(4)) < 0.1] = float("inf")
+    args, support = {"elliptic": ((0.05, 0.03, 25.0), 0.06),
+                     "tapered_sinc": ((2.5 / 60, 3.5 / 60), 3.75 / 60)}[shape]
+    plan = hcg.hcg_plan_ex(w.lon.to(DEV), w.lat.to(DEV), getattr(hcg.Kernel, shape)(*args), support,
+                           grid=w.grid)
+    cube = torch.full((nchan, ny, nx), 12345.0, device=DEV)
+    W = torch.full((nchan, ny, nx), -1.0, device=DEV)
+    print(f"{shape} n={n} C={nchan} {nx}x{ny}", flush=True)
+    hcg.hcg_grid_masked(plan, spec.to(DEV), cube, W)
+    torch.cuda.synchronize()
+    plan.destroy()
+    g = w.grid
+    cells = np.concatenate(sample_cells(g, seed=8, patches=4, patch=6))
+    iy, ix = np.divmod(cells, nx)
+    V, Wr, _ = oracle.grid_points(w.lon.numpy(), w.lat.numpy(), spec.numpy(),
+                                  g.lon0 + (ix - (nx - 1) / 2) * g.dlon,
+                                  g.lat0 + (iy - (ny - 1) / 2) * g.dlat, support,
+                                  getattr(oracle.Kernel, shape)(*args), masked=True)
+    idx = torch.from_numpy(cells).to(DEV)
+    Vg = cube.reshape(nchan, -1)[:, idx].cpu().numpy()
+    Wg = W.reshape(nchan, -1)[:, idx].cpu().numpy()
+    assert_cube_close(Vg, V.T, 1e-5, f"{shape} C={nchan}")
+    # (a sinc's weights change sign: a sum's error is one of the weights')
+    Wr = np.asarray(Wr).T
+    np.testing.assert_allclose(Wg, Wr, rtol=1e-6, atol=1e-6 * np.abs(Wr).max())
