@@ -118,23 +118,17 @@ constexpr double kWaveCand = 240.0;
 //     500,000 x 1024 -> 200 x 200 (2300): 4047 / 5094 / 3692; -> 400 x 400
 //     (570): 3734 / 4237 / 4061.  Flagged, 500,000 x 256 -> 400 x 400 (570):
 //     2081 / 2241 / 1744, 2M x 128 (2300): 7109 / 4299 / 3099.
-//     Their weights are split into pieces as well: supports of up to 11.7 sigma,
-//     whose weights (2^-100 at R) have three exact ones.
 //   - The tiles take a Gaussian's chords from the pair itself; the other two from
 //     offsets to the middle of a block (centred_chords).
 F32Kernel f32_kernel(const hcg_plan_s* p, int64_t C, bool mask) {
   if (p->kern.type == kGauss && !centred_chords(p)) return F32Kernel::kTile;
   const bool cached = (double)p->n * (double)C * 4.0 <= 100e6;
-  // pairs within R per cell if the samples cover the map evenly
-  const double cells = (double)p->grid.nx * p->grid.ny;
-  const double area = cells * std::fabs(p->grid.dlon * p->grid.dlat);
-  const double pairs =
-      area > 0.0 ? (double)p->n * kPi * p->support_deg * p->support_deg / area : 0.0;
   const int64_t slab = mask ? kBlockSlabFlagged : kBlockSlab;
   const double c2R = support_chord2(p);
-  const bool block = p->bmaxr && p->kern.type == kGauss && c2R < kNarrowChord2 &&
-                     p->kern.wscale * c2R * (1.0 + c2R) > -100.0 && !cached &&
-                     (mask ? C > 64 && pairs >= 500.0 : C >= 512 && pairs >= 2000.0) &&
+  const double pairs = p->bmaxr ? mean_pairs(p->n, p->grid, p->support_deg) : 0.0;
+  const bool block = p->bmaxr && !cached &&
+                     (mask ? C > 64 && pairs >= kBlockPairsFlagged
+                           : C >= 512 && pairs >= kBlockPairs) &&
                      (int64_t)p->bntx * p->bnty * ((C + slab - 1) / slab) >= kFewBlocks;
   if (block) return F32Kernel::kBlock;
   const double load = p->load.mean;

@@ -207,8 +207,9 @@ struct hcg_plan_s {
   uint32_t* nranges;   // [ntiles]
   uint32_t* ncand;     // [ntiles] candidates per tile
   hcg::TileLoad load;
-  // the same for blocks of 16 x 16 cells (gather_block.h); bmaxr = 0: none
-  // (cells given by their centres, or more rings than the range table holds)
+  // the same for blocks of 16 x 16 cells (gather_block.h); bmaxr = 0: none (a
+  // plan that no channel count takes blocks for, see takes_blocks; cells given
+  // by their centres; more rings than the range table holds)
   int32_t bntx, bnty, bmaxr;
   uint2* branges;
   uint32_t* bnranges;

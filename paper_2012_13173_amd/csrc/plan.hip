@@ -1192,7 +1192,12 @@ struct PlanBuilder {
                   nside, rings_d, kMaxRangesLimit / 2);
     const int maxr = 2 * (int)std::ceil(rings_d);
     const int bntx = (nx + kBlockCells - 1) / kBlockCells, bnty = (ny + kBlockCells - 1) / kBlockCells;
-    const int bmaxr = tg.grid ? block_max_ranges(std::fabs(tg.grid->dlat_deg) * kDeg2Rad, R, nside) : 0;
+    const GridGeom geom = tg.grid ? GridGeom{nx, ny, tg.grid->lon0_deg, tg.grid->lat0_deg,
+                                             tg.grid->dlon_deg, tg.grid->dlat_deg}
+                                  : GridGeom{nx, ny, 0.0, 0.0, 0.0, 0.0};
+    const int bmaxr = tg.grid && takes_blocks(kp, R, mean_pairs(n, geom, support_deg))
+                          ? block_max_ranges(std::fabs(geom.dlat) * kDeg2Rad, R, nside)
+                          : 0;
 
     // plan arena
     size_t off = 0;
@@ -1233,11 +1238,7 @@ struct PlanBuilder {
     p->passes = (key_bits + 7) / 8;
     p->ring_first = ring_first;
     p->ring_last = ring_last;
-    if (tg.grid)
-      p->grid = GridGeom{tg.grid->nx, tg.grid->ny, tg.grid->lon0_deg, tg.grid->lat0_deg,
-                         tg.grid->dlon_deg, tg.grid->dlat_deg};
-    else
-      p->grid = GridGeom{nx, ny, 0.0, 0.0, 0.0, 0.0};
+    p->grid = geom;
     p->centres = tg.grid ? 0 : 1;
     p->fwhm_deg = fwhm_nominal;
     p->support_deg = support_deg;
@@ -1519,7 +1520,9 @@ hcg_status plan_build_fields(int32_t nf, const hcg_field_desc* fd, const hcg_opt
     a.nc = take(sizeof(uint32_t) * ntiles);
     P.br.ntx = (P.grid.nx + kBlockCells - 1) / kBlockCells;
     P.br.nty = (P.grid.ny + kBlockCells - 1) / kBlockCells;
-    P.br.maxr = block_max_ranges(std::fabs(P.grid.dlat) * kDeg2Rad, P.support_rad, P.nside);
+    P.br.maxr = takes_blocks(kp[f], P.support_rad, mean_pairs(P.n, P.grid, fd[f].support_deg))
+                    ? block_max_ranges(std::fabs(P.grid.dlat) * kDeg2Rad, P.support_rad, P.nside)
+                    : 0;
     a.brng = take(sizeof(uint2) * (size_t)P.br.ntx * P.br.nty * P.br.maxr);
     a.bnr = take(sizeof(uint32_t) * (size_t)P.br.ntx * P.br.nty);
     a.flags = take(16);
