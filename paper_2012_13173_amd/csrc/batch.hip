@@ -434,12 +434,14 @@ void free_batch(hcg_batch_s* b) {
   delete b;
 }
 
-// Item segments of every class for slab width 256 * qw (256 for the BF16
-// hi+lo form, for fields whose rows cannot be read four elements at a time,
-// and for a narrow-support BF16, FP16 x scale or FP8 x scale class with a
-// field whose rows cannot be read eight at a time; one item per tile for the
-// few-channel class).  The work-item launch
-// gives a field slabs x (tiles rounded up to whole eighths) items.
+// Item segments of every class.  Tiles (8 x 8 cells) have slabs of 256 * qw
+// channels (256 for the BF16 hi+lo form, for fields whose rows cannot be read
+// four elements at a time, and for a narrow-support BF16, FP16 x scale or FP8 x
+// scale class with a field whose rows cannot be read eight at a time); blocks
+// of 16 x 16 cells have kBlockSlab; independent waves 64 or 128, on a tile or,
+// with several waves to a cell block, a quarter of one; the few-channel classes
+// one item per tile.  The work-item launch gives a field of the others slabs x
+// (tiles rounded up to whole eighths) items.
 hcg_status build_items(hcg_batch_s* b, const hcg_field_data* data, int qw, int cost_order,
                        int strategy, hipStream_t stream) {
   const size_t nf = b->plans.size();

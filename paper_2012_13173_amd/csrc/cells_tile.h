@@ -1,5 +1,5 @@
 // Device code of the few-channel gather (FP32 spectra, C <= 8, FP64 sums),
-// shared by the per-plan kernels (gather.hip) and the batch (batch.hip).
+// shared by the per-plan kernels (cells.hip) and the batch (batch.hip).
 //
 // A wave owns a sub-block of kNC cells of an 8 x 8 tile and walks the tile's
 // candidate list 64 candidates at a time, one candidate per lane; every lane

@@ -2,17 +2,18 @@
 // every output cell and channel, gather-side (Section 2.2: each cell pulls
 // the samples within its support, so no two workgroups write the same cell).
 //
-// Work decomposition: one workgroup per 8 x 8 tile of output cells (and per
-// 256- or 512-channel slab for many channels).  The tile's candidate samples
+// Work decomposition of the tile gather (the low-precision forms, and FP32 maps
+// that neither independent waves, gather_wave.h, nor 16 x 16-cell blocks,
+// gather_block.h, are faster for: f32_kernel): one workgroup per 8 x 8 tile of
+// output cells and 256- or 512-channel slab.  The tile's candidate samples
 // come from the plan's sorted-sample ranges and are staged in blocks of 64,
 // one block ahead:
 //   1. weights: FP64 great-circle distance of every (cell, candidate) pair
 //      of the block that a coarse per-cell-block test cannot rule out (from
 //      the chord of the unit vectors), exact support test, Gaussian weight
-//      (exponent in FP64; exp2 in FP32 for the matrix-core forms, in FP64 for
-//      the few-channel path), rounded to the operand type of the form; FP64
-//      sums of the weights per cell;
-//   2. accumulation: for many channels the block is a dense contraction
+//      (exponent in FP64, exp2 in FP32), rounded to the operand type of the
+//      form; FP64 sums of the weights per cell;
+//   2. accumulation: the block is a dense contraction
 //      U[cells x channels] += Wt[cells x 64] . S[64 x channels] done on the
 //      matrix cores with FP32 accumulation -- FP32 operands
 //      (v_mfma_f32_16x16x4_f32) or BF16 / FP16 / FP8 operands (16x16x32),
@@ -20,11 +21,11 @@
 //      the spectra are read in the caller's sample order through the plan's
 //      permutation, or (low-precision forms) from an encoding in the plan's
 //      sorted order whose groups of 8 samples are ready-made B operands;
-//      for a few FP32 channels a wave owns a sub-block of cells and a lane one
-//      candidate at a time, with FP64 sums (cells_tile.h);
 //   3. epilogue: V = U / W~ (W~ the sum of the weights actually multiplied,
 //      times the channel scale for the scaled forms), NaN where no sample is
 //      within the support; W map = FP64 sum of the unrounded weights.
+// For a few FP32 channels a wave owns a sub-block of cells and a lane one
+// candidate at a time, or a wave a tile, with FP64 sums (cells_tile.h).
 #include <cmath>
 #include <vector>
 
