@@ -36,7 +36,7 @@
 //     prepare first, so that the two waves of a SIMD use different units.
 // It measured 59.4 -> 50.7 ms (9.12M samples x 1024 -> 600 x 600 of 0.5', FWHM
 // 3') and, flagged, 4.63 -> 3.05 ms (1.14M x 256 -> 300 x 300).  What
-// bounds it now: 20 ms of matrix and 21 ms of vector instructions, which the
+// bounds it now: 18 ms of matrix and 21 ms of vector instructions, which the
 // two waves of a SIMD overlap only in part, and the barriers.
 #pragma once
 
