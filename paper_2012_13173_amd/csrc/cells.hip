@@ -16,16 +16,17 @@ namespace hcg {
 template <int kCM, bool kWide>
 constexpr int kCellsThreads = kCM <= 2 && !kWide ? 1024 : 512;
 
-template <int kCM, bool kMask, bool kWide, bool kGen, bool kExact>
+template <int kCM, bool kMask, bool kWide, bool kGen, bool kExact, bool kFew>
 __global__ void __launch_bounds__((kCellsThreads<kCM, kWide>)) k_gather_cells(const GatherArgs a, int subs, int nk) {
   extern __shared__ __align__(32) unsigned char s_dyn[];
-  const int per_tile = CellsShape<kCM, kMask, kGen>::kSubs / subs;
+  const int per_tile = CellsShape<kCM, kMask, kGen, kFew>::kSubs / subs;
   const int work = a.ntiles * per_tile;
   const int b = (int)wide_block(), eighth = (work + 7) >> 3;
   const int w = (b & 7) * eighth + (b >> 3);
   if ((b >> 3) >= eighth || w >= work) return;
   const int tile = w / per_tile;
-  cells_tile<kCM, kMask, kWide, kGen, kExact>(a, tile, (w - tile * per_tile) * subs, subs, nk, s_dyn);
+  cells_tile<kCM, kMask, kWide, kGen, kExact, kFew>(a, tile, (w - tile * per_tile) * subs, subs, nk,
+                                                    s_dyn);
 }
 
 template <int kCM, bool kMask, bool kWide, bool kGen>
@@ -35,6 +36,10 @@ __global__ void __launch_bounds__(64) k_gather_lane(const GatherArgs a) {
   if (tile < a.ntiles) cells_lane<kCM, kMask, kWide, kGen>(a, tile, s_dyn);
 }
 
+// Fewest tiles whose sixteen-cell sub-blocks, of eight waves each, fill the chip
+// with the other kernel shapes (two waves per SIMD): see CellsShape's kFew.
+constexpr int kCellsFewTiles = 64;
+
 // Waves per sub-block: no more than fill the chip (four per SIMD; at C = 1,
 // whose sub-blocks of sixteen cells do the most work per candidate, four
 // rounds of them) and two chunks of 64 candidates for each.  Waves 1 / 2 / 4 /
@@ -42,14 +47,17 @@ __global__ void __launch_bounds__(64) k_gather_lane(const GatherArgs a) {
 // 5168 of 651, C = 8: 42 / 48 / 64 / 135; 1352 of 64,000, C = 4: 711 / 429 / 426
 // / 593; 400 of 866, C = 8: 18 / 13 / 11 / 17; C = 1, 5776 of 7100: 353 / 315 /
 // 312 / 344 / 448, 576 of 79,000: eight 629, sixteen 567.
-template <int kCM, bool kMask, bool kWide, bool kGen, bool kExact>
+template <int kCM, bool kMask, bool kWide, bool kGen, bool kExact, bool kFew = false>
 static void launch_cells_kernel(const hcg_plan_s* p, const GatherArgs& a, hipStream_t stream) {
   if (cells_by_lane(p, kCM, kMask)) {
     k_gather_lane<kCM, kMask, kWide, kGen>
         <<<(unsigned)a.tiles_per_xcd * 8u, 64, cells_lane_lds_size<kCM>(a.maxr), stream>>>(a);
     return;
   }
-  using Sh = CellsShape<kCM, kMask, kGen>;
+  if constexpr (kGen && kCM == 1 && !kFew)
+    if (a.ntiles < kCellsFewTiles)
+      return launch_cells_kernel<kCM, kMask, kWide, kGen, kExact, true>(p, a, stream);
+  using Sh = CellsShape<kCM, kMask, kGen, kFew>;
   const int64_t all = (int64_t)a.ntiles * Sh::kSubs;
   constexpr int kMost = kCellsThreads<kCM, kWide> / 64;
   constexpr int64_t kWaves = kCM == 1 ? 16384 : 4096;
@@ -58,7 +66,7 @@ static void launch_cells_kernel(const hcg_plan_s* p, const GatherArgs& a, hipStr
   const int subs = nk >= 4 ? 1 : 4 / nk;
   const int64_t work = all / subs;
   const size_t lds = cells_lds_size<Sh::kNC, Sh::kS, kGen>(subs * nk, subs, a.maxr);
-  k_gather_cells<kCM, kMask, kWide, kGen, kExact>
+  k_gather_cells<kCM, kMask, kWide, kGen, kExact, kFew>
       <<<wide_grid((work + 7) / 8 * 8), 64 * subs * nk, lds, stream>>>(a, subs, nk);
 }
 

@@ -42,12 +42,14 @@ namespace hcg {
 // no more than about 80 registers of sums for any form but the flagged C = 8
 // (whose 128 spilled beside the weights of the other kernel shapes, kGen: two
 // cells there, 300,000 samples x 8 -> 150 x 150, tapered sinc: 2231 us with
-// four, so 1111).
-template <int kCM, bool kMask, bool kGen = false>
+// four, so 1111).  kFew: for maps of few tiles, half the cells at C = 1, whose
+// other shapes leave too few waves otherwise (50,000 samples -> 40 x 40, tapered
+// sinc: 180 us with sixteen, so 105; 361 tiles the same, 2500 1.1 times as long).
+template <int kCM, bool kMask, bool kGen = false, bool kFew = false>
 struct CellsShape {
   static constexpr int kW = kMask ? kCM : 1;
   static constexpr int kS = kCM + kW;
-  static constexpr int kNC = kS <= 2 ? 16 : kS <= 5 ? 8 : kGen && kS > 9 ? 2 : 4;
+  static constexpr int kNC = kS <= 2 ? (kFew ? 8 : 16) : kS <= 5 ? 8 : kGen && kS > 9 ? 2 : 4;
   static constexpr int kSubs = kTileCells / kNC;       // sub-blocks of a tile
   static constexpr int kSX = kNC == 16 ? 4 : kNC == 8 ? 4 : 2;  // cells of a sub-block in x
 };
@@ -141,10 +143,10 @@ __device__ __forceinline__ void cells_reduce(double (&v)[kN], int lane, int* at,
 // chunk of 64 candidates.  kWide = false: squared support chord below 1e-4
 // and no weight below the normal floats (the launchers check both).  kExact:
 // cells too far apart for centred_chords.
-template <int kCM, bool kMask, bool kWide, bool kGen, bool kExact = false>
+template <int kCM, bool kMask, bool kWide, bool kGen, bool kExact = false, bool kFew = false>
 __device__ inline void cells_tile(const GatherArgs& a, int tile, int sub0, int subs, int nk,
                                   unsigned char* base) {
-  using Sh = CellsShape<kCM, kMask, kGen>;
+  using Sh = CellsShape<kCM, kMask, kGen, kFew>;
   constexpr int kNC = Sh::kNC, kW = Sh::kW, kS = Sh::kS, kSX = Sh::kSX, kSY = kNC / kSX;
   constexpr int kN = kNC * kS;
   static_assert(kN <= 64, "one sum per lane after the reduction");

@@ -107,10 +107,11 @@ def test_tiles_of_few_candidates_match_the_oracle(n, nchan, nx, ny, cell, flags,
         torch.testing.assert_close(W_b, W, rtol=1e-6, atol=0)
 
 
-# sub-blocks of two cells by several waves and by one; one wave to a tile
+# sub-blocks of two cells (one channel: eight and sixteen) by several waves and
+# by one; one wave to a tile
 @pytest.mark.parametrize("n,nx,ny,cell", [(20_000, 45, 37, 0.75), (60_000, 150, 141, 0.5),
                                           (9000, 190, 141, 1.2)])
-@pytest.mark.parametrize("nchan", [5, 8])
+@pytest.mark.parametrize("nchan", [1, 5, 8])
 @pytest.mark.parametrize("shape", ["elliptic", "tapered_sinc"])
 def test_flagged_channels_of_the_other_kernel_shapes(n, nx, ny, cell, nchan, shape):
     w = synth.small_cube(n=n, nchan=nchan, nx=nx, ny=ny, cell_arcmin=cell, seed=1900 + nchan + nx)
