@@ -47,7 +47,8 @@ constexpr int kCellsFewTiles = 64;
 // 5168 of 651, C = 8: 42 / 48 / 64 / 135; 1352 of 64,000, C = 4: 711 / 429 / 426
 // / 593; 400 of 866, C = 8: 18 / 13 / 11 / 17; C = 1, 5776 of 7100: 353 / 315 /
 // 312 / 344 / 448, 576 of 79,000: eight 629, sixteen 567.
-template <int kCM, bool kMask, bool kWide, bool kGen, bool kExact, bool kFew = false>
+template <int kCM, bool kMask, bool kWide, bool kGen, bool kExact,
+          bool kFew = kCM == 1 && kWide && !kGen>
 static void launch_cells_kernel(const hcg_plan_s* p, const GatherArgs& a, hipStream_t stream) {
   if (cells_by_lane(p, kCM, kMask)) {
     k_gather_lane<kCM, kMask, kWide, kGen>

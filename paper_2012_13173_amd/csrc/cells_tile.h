@@ -42,9 +42,11 @@ namespace hcg {
 // no more than about 80 registers of sums for any form but the flagged C = 8
 // (whose 128 spilled beside the weights of the other kernel shapes, kGen: two
 // cells there, 300,000 samples x 8 -> 150 x 150, tapered sinc: 2231 us with
-// four, so 1111).  kFew: for maps of few tiles, half the cells at C = 1, whose
-// other shapes leave too few waves otherwise (50,000 samples -> 40 x 40, tapered
-// sinc: 180 us with sixteen, so 105; 361 tiles the same, 2500 1.1 times as long).
+// four, so 1111).  kFew: half the cells at C = 1, for wide circular Gaussians
+// (whose registers leave two waves per SIMD with sixteen: 1.5M samples -> 400 x
+// 400 of 5' 1159 us, so 1001; 50,000 -> 150 x 150 77 and 59) and for the other
+// shapes on maps of few tiles (50,000 -> 40 x 40, tapered sinc: 180 us, so 105;
+// 361 tiles the same, 2500 1.1 times as long).
 template <int kCM, bool kMask, bool kGen = false, bool kFew = false>
 struct CellsShape {
   static constexpr int kW = kMask ? kCM : 1;
@@ -470,8 +472,9 @@ __host__ inline bool cells_narrow(double c2R, const KernelParams& k) {
 // 5544 tiles of 2 to 64,000 candidates.  Sub-blocks / lanes: 2500 tiles, C = 1:
 // 52 candidates 26 / 12, 208: 39 / 33, 416: 52 / 57; C = 8: 52: 97 / 17, 416: 177
 // / 84; 323 tiles of 651, C = 8: 42 / 91; 64 of 231, C = 4: 9 / 30; 5544 of 2, C
-// = 8: 170 / 9; wide supports, C = 8 (whose sub-blocks keep two waves per SIMD),
-// 2500 tiles of 970: 592 / 371, of 4850: 2149 / 1684.  The other shapes' weights
+// = 8: 170 / 9; wide supports (whose sub-blocks keep two waves per SIMD), C = 8,
+// 2500 tiles of 970: 592 / 371, of 4850: 2149 / 1684; C = 4, of 970: 400 / 326,
+// flagged 569 / 481, of 4850 2097 / 2243.  The other shapes' weights
 // cost several times as much, and by sub-blocks as the cells that a candidate
 // reaches, `hits` of a tile's; fitted to 192 maps of 25 to 2500 tiles: elliptical,
 // 2500 tiles, C = 1: 160 candidates 159 / 112, 300: 183 / 205, 1530: 584 / 896;
@@ -480,9 +483,9 @@ __host__ inline bool cells_by_lane(const hcg_plan_s* p, int kCM, bool mask) {
   const double n = (double)p->ntx * p->nty, sums = mask ? 2.0 * kCM : kCM + 1.0;
   double wave = 0.11, lane = 4.8 + 0.5 * kCM;
   double tile = 0.005 + 0.0042 * kCM, sub = 2.3 + 0.5 * kCM, walk = 2.0;
+  const double R = p->support_rad, reach = 0.8 * p->tile_span + 2.0 * R;
+  const double hits = 3.9 * R * R / (reach * reach);
   if (p->kern.type != kGauss) {
-    const double side = p->tile_span * 0.8, R = p->support_rad, reach = side + 2.0 * R;
-    const double hits = 3.9 * R * R / (reach * reach);
     const double subs = sums <= 2.0 ? 4.0 : sums <= 5.0 ? 8.0 : sums <= 9.0 ? 16.0 : 32.0;
     const bool sinc = p->kern.type == kSinc;
     wave = (sinc ? 0.47 : 0.31) + 0.0085 * sums;
@@ -490,10 +493,17 @@ __host__ inline bool cells_by_lane(const hcg_plan_s* p, int kCM, bool mask) {
     tile = (sinc ? 0.0034 : 0.0023) * subs;
     sub = (sinc ? 14.0 : 4.8) + 0.65 * sums + 31.0 * hits;
     walk = 2.0 + 1.4 * sums;
-  } else if (kCM == 8 && !mask && !cells_narrow(support_chord2(p), p->kern)) {
-    wave = 0.2;
-    lane = 14.0;
-    sub = 18.0;
+  } else if (!cells_narrow(support_chord2(p), p->kern)) {
+    if (kCM == 4) {
+      wave = mask ? 0.22 : 0.17;
+      lane = mask ? 18.5 : 11.8;
+      tile = mask ? 0.055 : 0.033;
+      sub = mask ? 7.5 + 23.0 * hits : 5.7 + 16.5 * hits;
+    } else if (kCM == 8 && !mask) {
+      wave = 0.2;
+      lane = 14.0;
+      sub = 18.0;
+    }
   }
   const double cand = 1e-5 * p->load.mean * n;
   return std::max(wave * p->load.most, lane * cand) < tile * n + sub * cand + walk;
